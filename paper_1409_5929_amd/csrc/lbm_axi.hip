@@ -4,6 +4,7 @@
 // Kernels
 //   k_step     fused D2Q9-MRT + D2Q5 collide-stream, AA pattern, in place
 //              (lbm_axi_dev.h); optionally writes u_z, u_r, T for the check
+//   k_tile     several steps of a tile of the grid in LDS (lbm_axi_tile.h)
 //   k_resid    FP64 partial sums of the residual and of the Eq. (42) wall
 //              integrals, or of the heater sums of Eqs. (43)-(44) on an
 //              isoflux wall (wave shuffles, then LDS across the block's waves)
@@ -22,9 +23,10 @@
 // so that each of the 8 XCDs (blocks are dealt to XCDs round-robin) sweeps a
 // contiguous band of rows and neighbouring tiles share its L2.
 //
-// Stepping: runs of plain steps replay a captured HIP graph (kernels only);
+// Stepping: runs of plain steps go several at a time on LDS tiles where
+// plan_tiles says so, else they replay a captured HIP graph (kernels only);
 // steps that fall on a check, and every step while launches are timed, are
-// launched one by one.  Both give identical results.
+// launched one by one.  All give identical results.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -137,6 +139,14 @@ struct lbm_axi {
   bool wall_lanes = false;      // step kernels compute radial wall nodes on their own lanes
   long long* dclk = nullptr;    // device clock of captured step graphs
   int graph_steps = 32;         // steps per captured graph (0: no graphs)
+  // steps on LDS tiles (k_tile): 0 not planned yet, 1 planned, -1 not used
+  int tile_plan = 0;
+  int tile_m = 0, tile_h = 0;               // most steps per launch, rows per tile
+  int tile_nf = 0, tile_nt = 0, tile_lds = 0;  // fluid threads, threads, LDS bytes of a block
+  StepTile* dsteptiles = nullptr;  // own allocation
+  int nsteptiles = 0;
+  InstDev* ddesc_b = nullptr;      // descriptors of the second set of planes
+  std::vector<std::pair<void*, size_t>> planes_b;  // that set (and ddesc_b), in allocs
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -603,6 +613,9 @@ int launch_init(lbm_axi* h, int inst, const float* dinit, float T_init) {
 // of tiles (neighbouring rows share that XCD's L2).
 // Only instances flagged in h->active (all when it is empty) enter the launch
 // list; the per-instance list (field output) always holds every instance.
+bool build_step_tiles(lbm_axi* h);
+void drop_tile_plan(lbm_axi* h);
+
 int build_tiles(lbm_axi* h, int kz, int kz_odd) {
   // Per-instance list in instance order (field and start kernels, strips of kz)
   // and, for each parity, the XCD-ordered list of the running instances.
@@ -672,6 +685,10 @@ int build_tiles(lbm_axi* h, int kz, int kz_odd) {
   h->tile_count = count;
   h->kz = kz;
   h->kz_odd = kz_odd;
+  if (h->tile_plan > 0 && !build_step_tiles(h)) {
+    drop_tile_plan(h);
+    h->tile_plan = -1;
+  }
   return LBM_AXI_OK;
 }
 
@@ -736,6 +753,166 @@ void release(lbm_axi* h, void* p, size_t bytes) {
       h->bytes -= bytes;
       return;
     }
+}
+
+// ---- steps on LDS tiles (k_tile) ----
+
+void drop_tile_plan(lbm_axi* h) {
+  if (h->dsteptiles) (void)hipFree(h->dsteptiles);
+  h->dsteptiles = nullptr;
+  for (auto& b : h->planes_b) release(h, b.first, b.second);
+  h->planes_b.clear();
+  h->ddesc_b = nullptr;
+  h->tile_plan = 0;
+}
+
+// Tiles of every instance (only those of the running ones when live), and the
+// most boundary-node threads and LDS bytes that one takes.
+std::vector<StepTile> step_tiles(const lbm_axi* h, bool live, int& walls, size_t& lds) {
+  std::vector<StepTile> out;
+  walls = 0;
+  lds = 0;
+  for (int i = 0; i < h->n_inst; ++i) {
+    if (live && !(h->active.empty() || h->active[i])) continue;
+    const InstDev& D = h->hdesc[i];
+    std::vector<int> cj, ck;
+    tile_cuts(D, TILE_VW, h->tile_m, h->tile_h, cj, ck);
+    for (size_t a = 0; a + 1 < ck.size(); ++a)
+      for (size_t b = 0; b + 1 < cj.size(); ++b) {
+        out.push_back(StepTile{i, cj[b], cj[b + 1], ck[a], ck[a + 1], 0, 0, 0});
+        const TileRegion g = tile_load_region(D, out.back(), h->tile_m);
+        const size_t n = (size_t)(g.kh - g.kl) * TILE_VW;
+        lds = std::max(lds, h->storage == LBM_STORE_FP32 ? tile_bytes<float>(D.phi_mode != 0, n)
+                                                         : tile_bytes<__half>(D.phi_mode != 0, n));
+        walls = std::max(walls, tile_walls<true>(D, g).count);
+      }
+  }
+  return out;
+}
+
+// Uploads the running instances' tiles in the launch order of build_tiles.
+bool build_step_tiles(lbm_axi* h) {
+  int walls = 0;
+  size_t lds = 0;
+  const std::vector<StepTile> live = step_tiles(h, true, walls, lds);
+  h->tile_nt = TILE_NT;
+  h->tile_nf = TILE_NT - (walls + 63) / 64 * 64;
+  h->tile_lds = (int)lds;
+  if (h->tile_nf < TILE_NT / 2 || lds > (size_t)h->lds_per_block) return false;
+  const int T = (int)live.size(), per = T > 0 ? (T + 7) / 8 : 1;
+  std::vector<StepTile> order((size_t)per * 8, StepTile{-1, 0, 0, 0, 0, 0, 0, 0});
+  for (int b = 0; b < per * 8; ++b)
+    if ((b % 8) * per + b / 8 < T) order[b] = live[(b % 8) * per + b / 8];
+  StepTile* d = nullptr;
+  if (hipMalloc(&d, sizeof(StepTile) * order.size()) != hipSuccess) return false;
+  if (hipMemcpy(d, order.data(), sizeof(StepTile) * order.size(), hipMemcpyHostToDevice) != hipSuccess) {
+    (void)hipFree(d);
+    return false;
+  }
+  if (h->dsteptiles) (void)hipFree(h->dsteptiles);
+  h->dsteptiles = d;
+  h->nsteptiles = (int)order.size();
+  return true;
+}
+
+// Whether the handle's plain steps run on LDS tiles, and with which shape.
+// Steps per launch and rows per tile: while one tile per compute unit covers
+// the handle, long runs (8 steps) on the shortest tiles that still fit the 256
+// units; above that a launch is bound by its vector work, and the halo, worked on
+// again by each tile, is kept small: 6, then 4 steps on tiles of 28 rows.
+// Measured, us per step in single steps and on tiles: FP32 pipe 64 x 8 4.1 and
+// 1.8, annulus 100 x 200 7.2 and 2.9, 300^2 8.0 and 4.2, 632^2 14.1 and 10.3, 64
+// of 128^2 30.6 and 21.9, 1500 x 4000 154 and 110, the 1024 grids of the sweep
+// 1786 and 1319; FP16 200^2 9.0 and 6.3, 512^2 11.9 and 10.1.  In 16-bit storage
+// single steps take over where the tiles come to more than one for each compute
+// unit (550^2: 13.1 and 14.4, four of 300^2 12.2 and 14.7): they move half the
+// bytes, and the halo's roundings cost more.
+// Only handles with wall lanes take tiles: the tile kernel's radial walls are
+// theirs, bit for bit.
+void plan_tiles(lbm_axi* h) {
+  h->tile_plan = -1;
+  if (!h->wall_lanes) return;
+  const size_t esz = h->storage == LBM_STORE_FP32 ? 4 : 2;
+  size_t bytes = 0;
+  double nodes = 0.0;
+  for (const InstDev& D : h->hdesc) {
+    const bool flux = D.therm_rmin == THERM_FLUX || D.therm_rmax == THERM_FLUX;
+    // radially periodic columns wrap across tiles; the heated window of a flux wall is tested on unwrapped rows
+    if (D.side_rmin == SIDE_PERIODIC || (D.side_z == SIDE_PERIODIC && (flux || D.nz < 8))) return;
+    if (D.nr < 4 || D.nz < 4) return;
+    bytes += (size_t)D.plane * (14 * esz + (esz == 2 ? 4 : 0));
+    nodes += (double)D.nr * D.nz;
+  }
+  if (esz == 2 && nodes > 3e5) return;
+  // the second set of planes: at most a sixteenth of the device's memory
+  size_t free_b = 0, total = 0;
+  if (hipMemGetInfo(&free_b, &total) != hipSuccess || bytes > total / 16 || bytes > free_b / 4) return;
+  h->tile_m = nodes <= 1e5 ? 8 : (nodes <= 4e5 ? 6 : 4);
+  h->tile_h = 28;
+  if (nodes <= 1e5) {
+    int walls;
+    size_t lds;
+    for (h->tile_h = 5; h->tile_h < 28; ++h->tile_h)
+      if (step_tiles(h, false, walls, lds).size() <= 256) break;
+  }
+  std::vector<InstDev> b(h->hdesc);
+  hipError_t err = hipSuccess;
+  auto alloc = [&](size_t n) {
+    void* q = dalloc(h, n, &err);
+    if (q) h->planes_b.emplace_back(q, n);
+    return q;
+  };
+  bool ok = true;
+  for (InstDev& D : b) {
+    D.pop = alloc((size_t)14 * D.plane * esz);
+    D.g0 = esz == 4 ? (float*)D.pop + 9 * D.plane : (float*)alloc((size_t)D.plane * 4);
+    ok = D.pop && D.g0;
+    if (!ok) break;
+  }
+  if (ok) h->ddesc_b = (InstDev*)alloc(sizeof(InstDev) * h->n_inst);
+  ok = ok && h->ddesc_b &&
+       hipMemcpy(h->ddesc_b, b.data(), sizeof(InstDev) * h->n_inst, hipMemcpyHostToDevice) == hipSuccess &&
+       build_step_tiles(h);
+  if (!ok) {
+    (void)hipGetLastError();  // single steps need none of this
+    drop_tile_plan(h);
+  }
+  h->tile_plan = ok ? 1 : -1;
+}
+
+// Plain steps from the handle's level n that one run on tiles may take: an even
+// number from an even level up to n_end or the next check step, 0 where the
+// handle takes single steps.  A stream that is being captured gets single steps:
+// a replay must not depend on which planes hold the state.
+int tile_run(lbm_axi* h, long long n_end) {
+  const long long n = h->t;
+  if (h->timing || (n & 1)) return 0;
+  long long m = n_end - n;
+  if (h->check > 0) m = std::min(m, (n + h->check - 1) / h->check * h->check - n);
+  if (m < 4) return 0;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(h->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return 0;
+  if (h->tile_plan == 0) plan_tiles(h);
+  return h->tile_plan > 0 ? (int)std::min<long long>(m & ~1ll, 1 << 20) : 0;
+}
+
+// n (even, at least 4) steps on tiles in an even number of launches: the planes
+// alternate, and the state ends in those where it began.
+int tile_steps(lbm_axi* h, int n) {
+  const int L = (n + 2 * h->tile_m - 1) / (2 * h->tile_m) * 2;
+  int done = 0;
+  for (int i = 0; i < L; ++i) {
+    const int s = 2 * (int)((int64_t)(n / 2) * (i + 1) / L) - done;
+    const TileLaunch t{i & 1 ? h->ddesc_b : h->ddesc, i & 1 ? h->ddesc : h->ddesc_b, h->dsteptiles, h->dstatus,
+                       h->nsteptiles, h->tile_nf, h->tile_nt, h->tile_lds, h->stream};
+    const hipError_t e = h->storage == LBM_STORE_FP32 ? launch_tile_t<float>(t, s, h->t + done)
+                                                      : launch_tile_s16(h->storage, t, s, h->t + done);
+    const int rc = launch_result(e, "tile kernel launch");
+    if (rc) return rc;
+    done += s;
+  }
+  h->t += n;
+  return LBM_AXI_OK;
 }
 
 // One step of instance inst alone, in the AA layout of parity `odd` (plain
@@ -848,6 +1025,7 @@ void lbm_axi_destroy(lbm_axi* h) {
   if (h->dtiles) (void)hipFree(h->dtiles);
   if (h->dtiles_odd) (void)hipFree(h->dtiles_odd);
   if (h->dtiles_plain) (void)hipFree(h->dtiles_plain);
+  if (h->dsteptiles) (void)hipFree(h->dsteptiles);
   if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
   delete h;
 }
@@ -1064,6 +1242,7 @@ int lbm_axi_create(const lbm_axi_params* p, int32_t n_inst, const float* const* 
     }
     if (hipStreamSynchronize(h->stream) != hipSuccess)
       return bail(fail(LBM_AXI_EDEVICE, "start state"));
+    plan_tiles(h);
     *out = h;
     return LBM_AXI_OK;
   #undef HIPBAIL
@@ -1076,6 +1255,11 @@ int lbm_axi_step(lbm_axi* h, int32_t nsteps) {
     const long long t_end = h->t + nsteps;
     while (h->t < t_end) {
       const long long n = h->t;
+      if (const int m = tile_run(h, t_end)) {
+        const int rc = tile_steps(h, m);
+        if (rc) return rc;
+        continue;
+      }
       // A run of graph_steps plain steps from an even level with no check step
       // inside goes through the captured graph (not while timing launches).
       const int G = h->graph_steps;
@@ -1213,6 +1397,7 @@ int lbm_axi_set_storage(lbm_axi* h, int32_t storage, int32_t storage_shift) {
       return fail(LBM_AXI_EINVAL, "bad handle, storage type or storage_shift out of [0, 24]");
     HIPCHK(hipStreamSynchronize(h->stream));
     drop_graph(h);
+    drop_tile_plan(h);
     const int from = h->storage;
     const size_t esz_o = from == LBM_STORE_FP32 ? 4 : 2;
     const size_t esz_n = storage == LBM_STORE_FP32 ? 4 : 2;
@@ -1302,7 +1487,10 @@ int lbm_axi_set_wall_lanes(lbm_axi* h, int32_t mode, int32_t* on) {
     if (!h || mode < -1 || mode > 1) return fail(LBM_AXI_EINVAL, "bad handle or mode not in {-1, 0, 1}");
     HIPCHK(hipStreamSynchronize(h->stream));
     const bool want = mode < 0 ? default_wall_lanes(h) : mode == 1;
-    if (want != h->wall_lanes) drop_graph(h);  // captured graphs hold the other kernels
+    if (want != h->wall_lanes) {
+      drop_graph(h);  // captured graphs hold the other kernels
+      drop_tile_plan(h);
+    }
     h->wall_lanes = want;
     if (on) *on = want ? 1 : 0;
     return LBM_AXI_OK;

@@ -49,10 +49,14 @@
 
 namespace lbmaxi {
 
-enum { SIDE_WALL = 0, SIDE_AXIS = 1, SIDE_PERIODIC = 2, SIDE_FLOW = 3 };
+enum { SIDE_WALL = 0, SIDE_AXIS = 1, SIDE_PERIODIC = 2, SIDE_FLOW = 3, SIDE_UNWRAPPED = 4 };
 enum { THERM_FIXED = 0, THERM_ADIABATIC = 1, THERM_FLUX = 2 };
 enum { RUN = 0, CONVERGED = 1, DIVERGED = 2, STALLED = 3 };
-enum { MODE_STEP = 0, MODE_STEP_MACRO = 1, MODE_FIELDS = 2 };
+// MODE_TILE: a step without the boundary nodes the node owns; MODE_WALL: one of
+// these alone, (dr, dz) off its owner (j, k), with mac_slot = 3 (dr + 1) + dz + 1
+// (steps on LDS tiles).
+enum { MODE_STEP = 0, MODE_STEP_MACRO = 1, MODE_FIELDS = 2, MODE_TILE = 3, MODE_WALL = 4 };
+enum { ADDR_FLAT = 0, ADDR_BUF = 1, ADDR_TILE = 2 };  // population addressing: see PopAcc
 enum { MASK_RMIN = 1, MASK_RMAX = 2, MASK_ZMIN = 4, MASK_ZMAX = 8, MASK_AXIS = 16 };
 
 // Lanes of a step wave along r: the step's tiles start at multiples of it,
@@ -94,6 +98,8 @@ struct InstDev {
   float q_rmin, q_rmax;    // q'/k of isoflux radial walls
   int32_t qk_lo, qk_hi;    // heated columns qk_lo..qk_hi of an isoflux wall
   float u_in;              // inlet axial velocity with inlet/outlet columns
+  int32_t t_base, t_stride;  // tile descriptors only (tile_desc): offset of the first node of the
+                             // tile's planes, and the row stride of the instance's planes
 };
 
 // Optional outputs of the field kernel ([nz][nr], unpadded).
@@ -141,8 +147,8 @@ struct Store<__half> {
     const lbm_h2 h = __builtin_amdgcn_cvt_sr_f16_f32(lbm_h2{0, 0}, v * sc, r, false);
     p[i] = __builtin_bit_cast(__half, h[0]);
 #else
-    const uint32_t b = (__float_as_uint(v * sc) + (r >> 19)) & 0xFFFFE000u;  // 13 dropped bits
-    p[i] = __float2half_rn(__uint_as_float(b));
+    const uint32_t b = (__builtin_bit_cast(uint32_t, v * sc) + (r >> 19)) & 0xFFFFE000u;  // 13 dropped bits
+    p[i] = __float2half_rn(__builtin_bit_cast(float, b));
 #endif
   }
 };
@@ -160,8 +166,8 @@ struct Store<__hip_bfloat16> {
     const lbm_b2 h = __builtin_amdgcn_cvt_sr_bf16_f32(lbm_b2{0, 0}, v * sc, r, false);
     p[i] = __builtin_bit_cast(__hip_bfloat16, h[0]);
 #else
-    const uint32_t b = (__float_as_uint(v * sc) + (r >> 16)) & 0xFFFF0000u;  // 16 dropped bits
-    p[i] = __float2bfloat16(__uint_as_float(b));
+    const uint32_t b = (__builtin_bit_cast(uint32_t, v * sc) + (r >> 16)) & 0xFFFF0000u;  // 16 dropped bits
+    p[i] = __float2bfloat16(__builtin_bit_cast(float, b));
 #endif
   }
 };
@@ -203,8 +209,8 @@ __host__ __device__ inline int64_t slot_elem(int q, int64_t o, int64_t pl) {
 }
 
 // ---- population access --------------------------------------------------
-// PopAcc<S, false>: flat addressing through a pointer (64-bit addresses per
-// lane).  PopAcc<S, true>: buffer addressing, one descriptor in scalar
+// PopAcc<S, ADDR_FLAT>: flat addressing through a pointer (64-bit addresses per
+// lane).  PopAcc<S, ADDR_BUF>: buffer addressing, one descriptor in scalar
 // registers per instance and 32-bit byte offsets per lane (half the address
 // registers; the hardware also drops accesses outside the array), usable when
 // the population array is below 4 GiB.  The hardware takes the record count
@@ -237,10 +243,18 @@ __device__ inline void unpack(uint32_t w, float inv, float& f, float& g) {
   }
 }
 
-template <typename S, bool BUF>
+template <typename S, int BUF>
 struct PopAcc;
+// Index of node offset o in the planes a descriptor points to: a tile's planes
+// start at its first node.
+template <int BUF>
+__host__ __device__ inline int64_t plane_index(const InstDev& D, int64_t o) {
+  if constexpr (BUF == ADDR_TILE) return o - D.t_base;
+  return o;
+}
 template <typename S>
-struct PopAcc<S, false> {
+struct PopAcc<S, ADDR_FLAT> {
+  static constexpr int ADDR = ADDR_FLAT;
   S* P;
   int64_t pl;
   float inv, sc;
@@ -272,7 +286,8 @@ struct PopAcc<S, false> {
   }
 };
 template <typename S>
-struct PopAcc<S, true> {
+struct PopAcc<S, ADDR_BUF> {
+  static constexpr int ADDR = ADDR_BUF;
 #if defined(__HIP_DEVICE_COMPILE__)
   __amdgpu_buffer_rsrc_t rs;
 #endif
@@ -345,6 +360,22 @@ struct PopAcc<S, true> {
   }
 };
 
+// PopAcc<S, ADDR_TILE>: a tile's populations in LDS, through a tile descriptor
+// (tile_desc).  32-bit indices; same layout and roundings as the planes in HBM.
+template <typename S>
+struct PopAcc<S, ADDR_TILE> {
+  static constexpr int ADDR = ADDR_TILE;
+  PopAcc<S, ADDR_FLAT> A;
+  int base;
+  __host__ __device__ explicit PopAcc(const InstDev& D) : A(D), base(D.t_base) {}
+  __host__ __device__ float ld(int q, int64_t o) const { return A.ld(q, (int)o - base); }
+  __host__ __device__ void st(int q, int64_t o, float v, uint32_t r) const { A.st(q, (int)o - base, v, r); }
+  __host__ __device__ void ld_pair(int a, int64_t o, float& f, float& g) const { A.ld_pair(a, (int)o - base, f, g); }
+  __host__ __device__ void st_pair(int a, int64_t o, float f, float g, uint32_t rf, uint32_t rg) const {
+    A.st_pair(a, (int)o - base, f, g, rf, rg);
+  }
+};
+
 // Random bits of time level n (one value per step, shared by all nodes).
 __host__ __device__ inline uint32_t step_seed(long long n) {
   return mix32((uint32_t)n * 0x9E3779B9u + (uint32_t)((unsigned long long)n >> 32));
@@ -366,6 +397,20 @@ struct Dither {
 
 // Offset of row k in a plane (64-bit: planes of large grids pass 2^31).
 __host__ __device__ inline int64_t row_off(int k, int stride) { return (int64_t)k * stride; }
+
+// Identity of node (j, k), offset o, in the random stream: its offset in the
+// instance's planes.  Where a tile descriptor's rows are unwrapped (tile_desc)
+// its nz is 4 times the instance's.
+template <int BUF>
+__host__ __device__ inline uint32_t dither_id(const InstDev& D, int64_t o, int j, int k, int wl) {
+  if constexpr (BUF == ADDR_TILE) {
+    const int gnz = D.nz >> 2;
+    if (D.side_z == SIDE_UNWRAPPED) k -= k >= 2 * gnz ? 2 * gnz : (k >= gnz ? gnz : 0);
+    return (uint32_t)(k * D.t_stride + j - wl);
+  } else {
+    return (uint32_t)(o - wl);
+  }
+}
 
 // ---- per-column constants (r is fixed along a thread's z loop) -------------
 struct RowC {
@@ -541,10 +586,81 @@ __host__ __device__ inline void porosity(const InstDev& D, int64_t o, float& phi
   }
 }
 
+// a b + c in one rounding, as the compiler contracts it; on the host, which
+// contracts nothing, in two.
+__host__ __device__ inline float ffma(float a, float b, float c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_fmaf(a, b, c);
+#else
+  return a * b + c;
+#endif
+}
+__host__ __device__ inline float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+// a b + c d.  Which product of a sum the compiler contracts depends on the code
+// around it.  With EX the choice is written out, as the step kernels with wall
+// lanes make it (the first or the second product), so that the steps on LDS
+// tiles, compiled apart from them, give the same bits.
+template <bool EX>
+__host__ __device__ inline float sum_first(float a, float b, float c, float d) {
+  if constexpr (EX) return ffma(a, b, mul_rounded(c, d));
+  return a * b + c * d;
+}
+template <bool EX>
+__host__ __device__ inline float sum_second(float a, float b, float c, float d) {
+  if constexpr (EX) return ffma(c, d, mul_rounded(a, b));
+  return a * b + c * d;
+}
+// a b - c d, the same.
+template <bool EX>
+__host__ __device__ inline float diff_first(float a, float b, float c, float d) {
+  if constexpr (EX) return ffma(a, b, -mul_rounded(c, d));
+  return a * b - c * d;
+}
+
+// c + a b and c - a b, the same.
+template <bool EX>
+__host__ __device__ inline float add_product(float c, float a, float b) {
+  if constexpr (EX) return ffma(a, b, c);
+  return c + a * b;
+}
+template <bool EX>
+__host__ __device__ inline float sub_product(float c, float a, float b) {
+  if constexpr (EX) return ffma(-a, b, c);
+  return c - a * b;
+}
+// g_i - wt_i T of the moving temperature populations, the same: the step
+// kernels with wall lanes round wt_i theta (ROUND) for the axial ones.
+template <bool EX, bool ROUND>
+__host__ __device__ inline float thermal_neq(float t, float theta) {
+  if constexpr (EX) return ROUND ? t - mul_rounded(WT1, theta) : ffma(-WT1, theta, t);
+  return t - WT1 * theta;
+}
+
 // delta += M^{-1} X for moment increments X_1..X_8 (X_0 = 0); M^{-1} = M^T
 // diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4), M of Eq. (18).
+template <bool EX = false>
 __host__ __device__ inline void back_transform(float d[9], float X1, float X2, float X3, float X4,
                                                float X5, float X6, float X7, float X8) {
+  if constexpr (EX) {
+    constexpr float c6 = (float)(1.0 / 6.0);
+    const float b1 = mul_rounded(X1, (float)(1.0 / 36.0)), b2 = mul_rounded(X2, (float)(1.0 / 36.0));
+    const float b4 = mul_rounded(X4, (float)(1.0 / 12.0)), b6 = mul_rounded(X6, (float)(1.0 / 12.0));
+    const float ax = ffma(b2, -2.0f, -b1), dg = ffma(2.0f, b1, b2);
+    const float qr = ffma(X3, c6, b4), qz = ffma(X5, c6, b6);
+    d[0] += ffma(b2, 4.0f, -4.0f * b1);
+    d[1] += ffma(0.25f, X7, ffma(-2.0f, b4, ffma(X3, c6, ax)));
+    d[2] += ffma(-0.25f, X7, ffma(-2.0f, b6, ffma(X5, c6, ax)));
+    d[3] += ffma(0.25f, X7, ffma(2.0f, b4, ffma(X3, -c6, ax)));
+    d[4] += ffma(-0.25f, X7, ffma(2.0f, b6, ffma(X5, -c6, ax)));
+    d[5] += ffma(0.25f, X8, dg + qr + qz);
+    d[6] += ffma(-0.25f, X8, dg - qr + qz);
+    d[7] += ffma(0.25f, X8, dg - qr - qz);
+    d[8] += ffma(-0.25f, X8, dg + qr - qz);
+    return;
+  }
   const float a1 = X1 * (float)(1.0 / 36.0), a2 = X2 * (float)(1.0 / 36.0);
   const float a3 = X3 * (float)(1.0 / 6.0), a4 = X4 * (float)(1.0 / 12.0);
   const float a5 = X5 * (float)(1.0 / 6.0), a6 = X6 * (float)(1.0 / 12.0);
@@ -565,18 +681,19 @@ __host__ __device__ inline void back_transform(float d[9], float X1, float X2, f
 
 // Moment-space source S / r of Eq. (24) with F~ = (F_r + a_r, F_z) (Eq. 25);
 // unless printed, the a_r part is not divided by phi (see the header).
+template <bool EX = false>
 __host__ __device__ inline void source(bool printed, float rho, float ur, float uz, float iphi,
                                        float Fr, float Fz, float ar, float& S1, float& S7,
                                        float& S8) {
   if (printed) {
     const float Ftr = Fr + ar;
-    S1 = 6.0f * rho * (ur * Ftr + uz * Fz) * iphi;
-    S7 = 2.0f * rho * (ur * Ftr - uz * Fz) * iphi;
-    S8 = rho * (ur * Fz + uz * Ftr) * iphi;
+    S1 = 6.0f * rho * sum_first<EX>(ur, Ftr, uz, Fz) * iphi;
+    S7 = 2.0f * rho * diff_first<EX>(ur, Ftr, uz, Fz) * iphi;
+    S8 = rho * sum_first<EX>(ur, Fz, uz, Ftr) * iphi;
   } else {
-    S1 = 6.0f * rho * ((ur * Fr + uz * Fz) * iphi + ur * ar);
-    S7 = 2.0f * rho * ((ur * Fr - uz * Fz) * iphi + ur * ar);
-    S8 = rho * ((ur * Fz + uz * Fr) * iphi + uz * ar);
+    S1 = 6.0f * rho * sum_first<EX>(sum_first<EX>(ur, Fr, uz, Fz), iphi, ur, ar);
+    S7 = 2.0f * rho * sum_first<EX>(diff_first<EX>(ur, Fr, uz, Fz), iphi, ur, ar);
+    S8 = rho * sum_second<EX>(sum_second<EX>(ur, Fz, uz, Fr), iphi, uz, ar);
   }
 }
 
@@ -648,7 +765,7 @@ __host__ __device__ inline void wall_node(const InstDev& D, const A& P, const No
   const float inv_rb = frcp(rb);
   const int64_t ob = row_off(kb, D.stride) + jb;
   float phib, cDb, cFb;
-  porosity_of(D, D.phi_mode == 0 ? 0.0f : D.phi[ob], phib, cDb, cFb);
+  porosity_of(D, D.phi_mode == 0 ? 0.0f : D.phi[plane_index<A::ADDR>(D, ob)], phib, cDb, cFb);
   const uint8_t m = node_mask(D, jb, kb);
   float drho = B.drho, urb = 0.0f, uzb = 0.0f;
   const bool moving = D.side_z == SIDE_FLOW && !(m & (MASK_RMIN | MASK_RMAX));  // inlet or outlet
@@ -753,11 +870,110 @@ __host__ __device__ inline void wall_node(const InstDev& D, const A& P, const No
   }
 }
 
+// wall_node for one boundary node on a lane of its own (steps on LDS tiles), any
+// (dr, dz) in one pass.  The compiler contracts wall_node's products as the
+// code around it falls; here each contraction is written out, the ones that the
+// step kernels' owners make, so that both give the same bits.
+template <typename S, bool ODD, bool WL, typename A>
+__host__ __device__ inline void wall_node_alone(const InstDev& D, const A& P, const NodeState& B, float rB, int j,
+                                                int k, int dr, int dz, Dither& rn) {
+#pragma clang fp contract(off)
+  const int jb = j + dr, kb = k + dz;
+  const float rb = rB + (float)dr;
+  const float inv_rb = frcp(rb);
+  const int64_t ob = row_off(kb, D.stride) + jb;
+  float phib, cDb, cFb;
+  porosity_of(D, D.phi_mode == 0 ? 0.0f : D.phi[plane_index<A::ADDR>(D, ob)], phib, cDb, cFb);
+  const uint8_t m = node_mask(D, jb, kb);
+  float drho = B.drho, urb = 0.0f, uzb = 0.0f;
+  const bool moving = D.side_z == SIDE_FLOW && !(m & (MASK_RMIN | MASK_RMAX));
+  if (moving) {
+    if (m & MASK_ZMIN) {
+      uzb = D.u_in;
+    } else {
+      drho = 0.0f;
+      urb = B.ur;
+      uzb = B.uz;
+    }
+  }
+  const float rhob = 1.0f + drho;
+  float Tb = B.T, qf;
+  if ((m & MASK_RMIN) && D.therm_rmin == THERM_FIXED) Tb = D.T_rmin;
+  else if ((m & MASK_RMAX) && D.therm_rmax == THERM_FIXED) Tb = D.T_rmax;
+  else if ((m & MASK_ZMIN) && D.therm_z == THERM_FIXED) Tb = D.T_zmin;
+  else if ((m & MASK_ZMAX) && D.therm_z == THERM_FIXED && D.side_z != SIDE_FLOW) Tb = D.T_zmax;
+  else if (flux_node(D, m, kb, qf)) Tb = B.T + qf;
+
+  const float q = rB * inv_rb;
+  const float hb = 0.5f * CS2 * inv_rb, cr = CS2 * inv_rb;
+  const float Gz = ffma(D.gbeta, Tb - D.T_ref, D.accel_z);
+  const float he = 1.0f - 0.5f * D.s_e, hp = 1.0f - 0.5f * D.s_eps, hj = 1.0f - 0.5f * D.s_j;
+  const float hq = 1.0f - 0.5f * D.s_q, hn = 1.0f - 0.5f * D.s_nu;
+  float X1 = (1.0f - D.s_e) * q * B.n1, X2 = (1.0f - D.s_eps) * q * B.n2;
+  float X3 = (1.0f - D.s_j) * q * B.n3, X4 = (1.0f - D.s_q) * q * B.n4;
+  float X5 = (1.0f - D.s_j) * q * B.n5, X6 = (1.0f - D.s_q) * q * B.n6;
+  float X7 = (1.0f - D.s_nu) * q * B.n7, X8 = (1.0f - D.s_nu) * q * B.n8;
+  // g^neq of the owner times 1 - omega(r_b)
+  const float T5 = 5.0f * WT1 * B.T;
+  const float om1 = ffma(D.tau_T, inv_rb, 1.0f), om3 = ffma(-D.tau_T, inv_rb, 1.0f), om2 = 1.0f - D.omc;
+  constexpr bool RND = WL;
+  const float q2 = thermal_neq<true, RND>(B.t[2], B.theta), q4 = thermal_neq<true, RND>(B.t[4], B.theta);
+  float tg[5];
+  tg[1] = ffma(-D.omc, om1, 1.0f) * ffma(-T5, B.ur, ffma(-WT1, B.theta, B.t[1]));
+  tg[2] = om2 * ffma(-T5, B.uz, q2);
+  tg[3] = ffma(-D.omc, om3, 1.0f) * ffma(T5, B.ur, ffma(-WT1, B.theta, B.t[3]));
+  tg[4] = om2 * ffma(T5, B.uz, q4);
+  if (!moving) {
+    const float S3 = ffma(phib, D.accel_r, cr) * rhob, S5 = rhob * phib * Gz;
+    X3 = ffma(hj, S3, X3) - hb;
+    X4 = ffma(-hq, S3, X4) + hb;
+    X5 = ffma(hj, S5, X5);
+    X6 = ffma(-hq, S5, X6);
+    for (int i = 1; i < 5; ++i) tg[i] = ffma(Tb - D.T_s, WT1, tg[i]);
+  } else {
+    const float iphib = frcp(phib);
+    const float ur2 = urb * urb, uz2 = uzb * uzb, u2 = ffma(uzb, uzb, ur2);
+    const float drag = ffma(cFb, fsqrt(u2), cDb);
+    const float Frb = ffma(phib, D.accel_r, -(urb * drag)), Fzb = ffma(phib, Gz, -(uzb * drag));
+    const float arb = ffma(-inv_rb, 2.0f * D.c_tau * urb * inv_rb, cr);
+    const float zz = uzb * Fzb, rz = urb * Fzb, Ft = Frb + arb;
+    float S1, S7, S8;
+    if (D.src_printed != 0) {
+      S1 = 6.0f * rhob * ffma(urb, Ft, zz) * iphib;
+      S7 = 2.0f * rhob * ffma(urb, Ft, -zz) * iphib;
+      S8 = rhob * ffma(uzb, Ft, rz) * iphib;
+    } else {
+      const float ua = urb * arb;
+      S1 = 6.0f * rhob * ffma(iphib, ffma(urb, Frb, zz), ua);
+      S7 = 2.0f * rhob * ffma(iphib, ffma(urb, Frb, -zz), ua);
+      S8 = rhob * ffma(uzb, arb, iphib * ffma(uzb, Frb, rz));
+    }
+    const float S3 = rhob * Ft, S5 = rhob * Fzb, r3 = 3.0f * rhob * u2;
+    X1 = ffma(he, S1, ffma(iphib, r3, X1));
+    X2 = ffma(-hp, S1, ffma(-iphib, r3, X2));
+    X3 = ffma(hj, S3, ffma(urb, rhob, X3)) - hb;
+    X4 = ffma(-hq, S3, ffma(-urb, rhob, X4)) + hb;
+    X5 = ffma(hj, S5, ffma(uzb, rhob, X5));
+    X6 = ffma(-hq, S5, ffma(-uzb, rhob, X6));
+    X7 = ffma(hn, S7, ffma(iphib, rhob * (ur2 - uz2), X7));
+    X8 = ffma(hn, S8, ffma(iphib, rhob * urb * uzb, X8));
+    const float wT = WT1 * Tb, t5 = wT * 5.0f, base = WT1 * (Tb - D.T_s), psib = -urb * inv_rb;
+    tg[1] = ffma(psib, ffma(urb, t5, wT), tg[1] + ffma(urb, t5, base));
+    tg[2] = ffma(psib, ffma(uzb, t5, wT), tg[2] + ffma(uzb, t5, base));
+    tg[3] = ffma(psib, ffma(-urb, t5, wT), tg[3] + ffma(-urb, t5, base));
+    tg[4] = ffma(psib, ffma(-uzb, t5, wT), tg[4] + ffma(-uzb, t5, base));
+  }
+  const float w1 = W1 * drho, w5 = W5 * drho;
+  float d[9] = {0.0f, w1, w1, w1, w1, w5, w5, w5, w5};
+  back_transform<true>(d, X1, X2, X3, X4, X5, X6, X7, X8);
+  store_wall<S, ODD>(D, P, jb, kb, d, tg, rn);
+}
+
 // The populations arriving at fluid node (j, k) (as stored, unscaled to
 // FP32) and its porosity value.  Each slot is read and written by one node
 // only in a step, so these loads may be issued before earlier nodes of the
 // same thread are updated.
-template <typename S, bool ODD, bool BUF = false>
+template <typename S, bool ODD, int BUF = ADDR_FLAT>
 __host__ __device__ inline void node_load(const InstDev& D, const RowC& R, int j, int k, float s[9],
                                           float t[5], float& phi_raw) {
   const PopAcc<S, BUF> P(D);
@@ -773,7 +989,7 @@ __host__ __device__ inline void node_load(const InstDev& D, const RowC& R, int j
     if (!ODD) {
 #pragma unroll
       for (int q = 0; q < 9; ++q) s[q] = P.ld(q, o);
-      t[0] = D.g0[o];
+      t[0] = D.g0[plane_index<BUF>(D, o)];
 #pragma unroll
       for (int q = 1; q < 5; ++q) t[q] = P.ld(9 + q, o);
     } else {
@@ -787,7 +1003,7 @@ __host__ __device__ inline void node_load(const InstDev& D, const RowC& R, int j
       s[6] = P.ld(8, rowm + cp);
       s[7] = P.ld(5, rowp + cp);
       s[8] = P.ld(R.mir ? 5 : 6, rowp + cm);
-      t[0] = D.g0[o];
+      t[0] = D.g0[plane_index<BUF>(D, o)];
       t[1] = P.ld(R.mir ? 10 : 12, row0 + cm);
       t[2] = P.ld(13, rowm + j);
       t[3] = P.ld(10, row0 + cp);
@@ -801,7 +1017,7 @@ __host__ __device__ inline void node_load(const InstDev& D, const RowC& R, int j
       for (int a = 0; a < 4; ++a) P.ld_pair(a, o, s[a + 1], t[a + 1]);
 #pragma unroll
       for (int q = 5; q < 9; ++q) s[q] = P.ld(q, o);
-      t[0] = D.g0[o];
+      t[0] = D.g0[plane_index<BUF>(D, o)];
     } else {
       const int64_t cm = R.cm, cp = R.cp;
       s[0] = P.ld(0, o);
@@ -813,10 +1029,10 @@ __host__ __device__ inline void node_load(const InstDev& D, const RowC& R, int j
       s[6] = P.ld(8, rowm + cp);
       s[7] = P.ld(5, rowp + cp);
       s[8] = P.ld(R.mir ? 5 : 6, rowp + cm);
-      t[0] = D.g0[o];
+      t[0] = D.g0[plane_index<BUF>(D, o)];
     }
   }
-  phi_raw = D.phi_mode == 0 ? 0.0f : D.phi[o];
+  phi_raw = D.phi_mode == 0 ? 0.0f : D.phi[plane_index<BUF>(D, o)];
 }
 
 // Slots of the populations arriving at fluid node (j, k) in the AA layout of
@@ -868,7 +1084,7 @@ __host__ __device__ inline void node_slots(const InstDev& D, const RowC& R, int 
 // in one word), into the slot it came from, its bits XORed with key: key = 0
 // leaves the state as it was, and the compiler cannot drop the stores.  The
 // porosity value is folded into the g_0 store the same way.
-template <typename S, bool ODD, bool BUF>
+template <typename S, bool ODD, int BUF>
 __device__ inline void pattern_store(const InstDev& D, const RowC& R, int j, int k, const float s[9],
                                      const float t[5], float ph, uint32_t key) {
   constexpr int OPP[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
@@ -914,6 +1130,7 @@ __device__ inline void pattern_store(const InstDev& D, const RowC& R, int j, int
 // wl: directions 1, 5, 8 or 3, 6, 7, and the D2Q5 one) to the slots its
 // fluid neighbours read; its other populations go to the wall column's own
 // slots, which no fluid node reads (node_update_loaded).
+template <bool EX = false, bool S16 = false>
 __host__ __device__ inline void wall_lane_inputs(const InstDev& D, const NodeState& B, const float t[5],
                                                  float rB, int wl, int k, int64_t ob, float d[9],
                                                  float X[8], float& ga, float& Tb) {
@@ -927,25 +1144,36 @@ __host__ __device__ inline void wall_lane_inputs(const InstDev& D, const NodeSta
   else if (th == THERM_FLUX && k >= D.qk_lo && k <= D.qk_hi) Tb = B.T + (lo ? D.q_rmin : D.q_rmax);
   const float drho = B.drho, rhob = 1.0f + drho;
   const float q = rB * inv_rb;
-  const float hb = 0.5f * CS2 * inv_rb;
+  const float hb = EX ? mul_rounded(0.5f * CS2, inv_rb) : 0.5f * CS2 * inv_rb;
   const float Gz = D.gbeta * (Tb - D.T_ref) + D.accel_z;
-  const float S3 = rhob * (phib * D.accel_r + CS2 * inv_rb), S5 = rhob * phib * Gz;
+  const float S3 = rhob * (S16 ? sum_second<EX>(phib, D.accel_r, CS2, inv_rb) : sum_first<EX>(phib, D.accel_r, CS2, inv_rb));
+  const float S5 = rhob * phib * Gz;
   X[0] = (1.0f - D.s_e) * q * B.n1;
   X[1] = (1.0f - D.s_eps) * q * B.n2;
-  X[2] = (1.0f - D.s_j) * q * B.n3 + (1.0f - 0.5f * D.s_j) * S3 - hb;
-  X[3] = (1.0f - D.s_q) * q * B.n4 - (1.0f - 0.5f * D.s_q) * S3 + hb;
-  X[4] = (1.0f - D.s_j) * q * B.n5 + (1.0f - 0.5f * D.s_j) * S5;
-  X[5] = (1.0f - D.s_q) * q * B.n6 - (1.0f - 0.5f * D.s_q) * S5;
+  X[2] = sum_first<EX>((1.0f - D.s_j) * q, B.n3, 1.0f - 0.5f * D.s_j, S3);
+  X[3] = diff_first<EX>((1.0f - D.s_q) * q, B.n4, 1.0f - 0.5f * D.s_q, S3);
+  if constexpr (EX && S16) {
+    X[2] = ffma(-0.5f * CS2, inv_rb, X[2]);
+    X[3] = ffma(0.5f * CS2, inv_rb, X[3]);
+  } else {
+    X[2] -= hb;
+    X[3] += hb;
+  }
+  X[4] = sum_first<EX>((1.0f - D.s_j) * q, B.n5, 1.0f - 0.5f * D.s_j, S5);
+  X[5] = diff_first<EX>((1.0f - D.s_q) * q, B.n6, 1.0f - 0.5f * D.s_q, S5);
   X[6] = (1.0f - D.s_nu) * q * B.n7;
   X[7] = (1.0f - D.s_nu) * q * B.n8;
-  d[0] = W0 * drho;
+  d[0] = EX ? mul_rounded(W0, drho) : W0 * drho;
 #pragma unroll
-  for (int i = 1; i < 5; ++i) d[i] = W1 * drho;
+  for (int i = 1; i < 5; ++i) d[i] = EX ? mul_rounded(W1, drho) : W1 * drho;
 #pragma unroll
-  for (int i = 5; i < 9; ++i) d[i] = W5 * drho;
-  const float om = D.omc * (1.0f + fs * D.tau_T * inv_rb);
+  for (int i = 5; i < 9; ++i) d[i] = EX ? mul_rounded(W5, drho) : W5 * drho;
   const float tB = lo ? t[1] : t[3];
-  ga = WT1 * (Tb - D.T_s) + (1.0f - om) * (tB - WT1 * B.theta - 5.0f * WT1 * B.T * fs * B.ur);
+  if constexpr (EX)
+    ga = ffma(ffma(-D.omc, ffma(fs * D.tau_T, inv_rb, 1.0f), 1.0f), ffma(-(5.0f * WT1 * B.T * fs), B.ur, tB - mul_rounded(WT1, B.theta)),
+              mul_rounded(WT1, Tb - D.T_s));
+  else
+    ga = WT1 * (Tb - D.T_s) + (1.0f - D.omc * (1.0f + fs * D.tau_T * inv_rb)) * (tB - WT1 * B.theta - 5.0f * WT1 * B.T * fs * B.ur);
 }
 
 // Whether the predicate holds on any lane of the wave (on the host, for this
@@ -959,14 +1187,39 @@ __host__ __device__ inline bool any_lane(bool p) {
 #endif
 }
 
+// Advances the random stream of owner (j, k) past its boundary nodes that come
+// before (dr, dz), in the order in which the owner takes them (the end of
+// node_update_loaded): one draw for each population that reaches a fluid node.
+template <bool WL>
+__host__ __device__ inline void owned_draws(const InstDev& D, int j, int k, int dr, int dz, Dither& rn) {
+  constexpr int EXr[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
+  constexpr int EZr[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
+  for (int code = 0; code < 3 * (dr + 1) + dz + 1; ++code) {
+    const int br = code / 3 - 1, bz = code % 3 - 1;
+    if (br == 0 && bz == 0) continue;
+    if ((br == -1 && !(D.side_rmin == SIDE_WALL && j == 1)) || (br == 1 && !(D.side_rmax == SIDE_WALL && j == D.nr - 2)))
+      continue;
+    if (bz == 0 && WL && (br == -1 || wall_lane_rmax(D))) continue;
+    if ((bz == -1 && !(z_bounded(D) && k == 1)) || (bz == 1 && !(z_bounded(D) && k == D.nz - 2))) continue;
+    for (int i = 1; i < 13; ++i) {
+      const int q = i < 9 ? i : i - 8;
+      int jd = j + br + EXr[q], kd = k + bz + EZr[q];
+      if (jd < 0 && D.side_rmin == SIDE_AXIS) jd = 0;
+      if (fluid_dest(D, jd, kd)) (void)rn.next();
+    }
+  }
+}
+
 // One fluid node (j, k) at one time step, from its loaded populations s, t
 // and porosity value.  seed: random bits of this step for stochastic
 // rounding of 16-bit storage.
-template <typename S, bool ODD, int MODE, bool BUF = false, bool WL = false>
+template <typename S, bool ODD, int MODE, int BUF = ADDR_FLAT, bool WL = false>
 __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC& R, int j, int k,
                                                    int mac_slot, const FieldOut& fo, uint32_t seed,
                                                    const float s[9], const float t_in[5],
                                                    float phi_raw, int wl = 0) {
+  // steps on LDS tiles contract as the step kernels do
+  constexpr bool EX = MODE == MODE_WALL || MODE == MODE_TILE;
   const PopAcc<S, BUF> P(D);
   const int64_t pl = D.plane;
   const int st = D.stride;
@@ -977,7 +1230,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   }
   const int64_t rowm = row_off(km, st), row0 = row_off(k, st), rowp = row_off(kp, st);
   const int64_t o = row0 + j;
-  Dither rn(mix32(seed ^ (uint32_t)(o - wl)));  // a wall lane draws its wall node's stream
+  Dither rn(mix32(seed ^ dither_id<BUF>(D, o, j, k, wl)));  // a wall lane draws its wall node's stream
   float t[5] = {t_in[0], t_in[1], t_in[2], t_in[3], t_in[4]};
   float phi, cD, cF;
   porosity_of(D, phi_raw, phi, cD, cF);
@@ -987,12 +1240,12 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   d[0] = s[0];
   d[2] = s[2];
   d[4] = s[4];
-  d[1] = s[1] * R.rp + R.op1;
-  d[5] = s[5] * R.rp + R.op5;
-  d[8] = s[8] * R.rp + R.op5;
-  d[3] = s[3] * R.rm + R.om1;
-  d[6] = s[6] * R.rm + R.om5;
-  d[7] = s[7] * R.rm + R.om5;
+  d[1] = EX ? ffma(s[1], R.rp, R.op1) : s[1] * R.rp + R.op1;
+  d[5] = EX ? ffma(s[5], R.rp, R.op5) : s[5] * R.rp + R.op5;
+  d[8] = EX ? ffma(s[8], R.rp, R.op5) : s[8] * R.rp + R.op5;
+  d[3] = EX ? ffma(s[3], R.rm, R.om1) : s[3] * R.rm + R.om1;
+  d[6] = EX ? ffma(s[6], R.rm, R.om5) : s[6] * R.rm + R.om5;
+  d[7] = EX ? ffma(s[7], R.rm, R.om5) : s[7] * R.rm + R.om5;
 
   // ---- macroscopic values ------------------------------------------------
   NodeState B;
@@ -1006,15 +1259,15 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   B.theta = t[0] + t[1] + t[2] + t[3] + t[4];               // T - T_s, Eq. (38)
   B.T = D.T_s + B.theta;
   const float Gr = D.accel_r;
-  const float Gz = D.gbeta * B.theta + D.az_s;              // Eq. (7)
-  const float vr = (Jr + R.hcs2r * B.drho) * inv_rho + 0.5f * phi * Gr;  // Eq. (29) / r
-  const float vz = Jz * inv_rho + 0.5f * phi * Gz;
+  const float Gz = EX ? ffma(D.gbeta, B.theta, D.az_s) : D.gbeta * B.theta + D.az_s;  // Eq. (7)
+  const float vr = sum_first<EX>(add_product<EX>(Jr, R.hcs2r, B.drho), inv_rho, 0.5f * phi, Gr);  // Eq. (29) / r
+  const float vz = sum_first<EX>(Jz, inv_rho, 0.5f * phi, Gz);
   const float lr0 = R.lr0b + 0.25f * cD;                    // Eq. (30) / r
   const float lz0 = 0.5f + 0.25f * cD;
   const float l1 = 0.5f * cF;
-  const float vm = fsqrt(vr * vr + vz * vz);
-  B.ur = vr * frcp(lr0 + fsqrt(lr0 * lr0 + l1 * vm));       // Eq. (28)
-  B.uz = vz * frcp(lz0 + fsqrt(lz0 * lz0 + l1 * vm));
+  const float vm = fsqrt(sum_second<EX>(vr, vr, vz, vz));
+  B.ur = vr * frcp(lr0 + fsqrt(sum_first<EX>(lr0, lr0, l1, vm)));       // Eq. (28)
+  B.uz = vz * frcp(lz0 + fsqrt(sum_first<EX>(lz0, lz0, l1, vm)));
   const float ur = B.ur, uz = B.uz, rho = B.rho;
 
   if (MODE == MODE_STEP_MACRO) {
@@ -1034,24 +1287,41 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   }
 
   // ---- forces (Eq. 6) and the axisymmetric correction (Eq. 25) -----------
-  const float um = fsqrt(ur * ur + uz * uz);
-  const float drag = cD + cF * um;
-  const float Fr = phi * Gr - drag * ur;
-  const float Fz = phi * Gz - drag * uz;
-  const float ar = R.ar0 - R.ar1 * ur;
+  const float uu = sum_first<EX>(ur, ur, uz, uz);
+  const float um = fsqrt(uu);
+  const float drag = add_product<EX>(cD, cF, um);
+  const float Fr = diff_first<EX>(phi, Gr, drag, ur);
+  const float Fz = diff_first<EX>(phi, Gz, drag, uz);
+  const float ar = sub_product<EX>(R.ar0, R.ar1, ur);
 
   // ---- moments of d and the non-equilibrium part (Eqs. 16-20) -----------
   const float iphi = frcp(phi);
-  const float ru2 = rho * (ur * ur + uz * uz) * iphi;
-  B.n1 = (-4.0f * d[0] - sa + 2.0f * sd) + 2.0f * B.drho - 3.0f * ru2;
-  B.n2 = (4.0f * d[0] - 2.0f * sa + sd) - B.drho + 3.0f * ru2;
+  const float ru2 = rho * uu * iphi;
+  B.n1 = sub_product<EX>((-4.0f * d[0] - sa + 2.0f * sd) + 2.0f * B.drho, 3.0f, ru2);
+  B.n2 = add_product<EX>((4.0f * d[0] - 2.0f * sa + sd) - B.drho, 3.0f, ru2);
   const float m4 = -2.0f * d[1] + 2.0f * d[3] + d[5] - d[6] - d[7] + d[8];
-  B.n3 = (Jr - R.hcs2r) - rho * ur;
-  B.n4 = (m4 + R.hcs2r) + rho * ur;
-  B.n5 = Jz - rho * uz;
-  B.n6 = (-2.0f * d[2] + 2.0f * d[4] + d[5] + d[6] - d[7] - d[8]) + rho * uz;
-  B.n7 = (d[1] - d[2] + d[3] - d[4]) - rho * (ur * ur - uz * uz) * iphi;
-  B.n8 = (d[5] - d[6] + d[7] - d[8]) - rho * ur * uz * iphi;
+  B.n3 = sub_product<EX>(Jr - R.hcs2r, rho, ur);
+  B.n4 = add_product<EX>(m4 + R.hcs2r, rho, ur);
+  B.n5 = sub_product<EX>(Jz, rho, uz);
+  B.n6 = add_product<EX>(-2.0f * d[2] + 2.0f * d[4] + d[5] + d[6] - d[7] - d[8], rho, uz);
+  if constexpr (EX)
+    B.n7 = ffma(-iphi, rho * (mul_rounded(ur, ur) - mul_rounded(uz, uz)), d[1] - d[2] + d[3] - d[4]);
+  else
+    B.n7 = (d[1] - d[2] + d[3] - d[4]) - rho * (ur * ur - uz * uz) * iphi;
+  B.n8 = sub_product<EX>(d[5] - d[6] + d[7] - d[8], rho * ur * uz, iphi);
+
+  if constexpr (MODE == MODE_WALL) {
+    const int dr = mac_slot / 3 - 1, dz = mac_slot % 3 - 1;
+    for (int q = 0; q < 5; ++q) B.t[q] = t[q];
+    if constexpr (sizeof(S) == 2) {
+      // the owner's random stream first serves its own 13 stores and its
+      // boundary nodes before this one
+      for (int i = 0; i < 13; ++i) (void)rn.next();
+      owned_draws<WL>(D, j, k, dr, dz, rn);
+    }
+    wall_node_alone<S, ODD, WL>(D, P, B, R.r, j, k, dr, dz, rn);
+    return;
+  }
 
   // Where the stores go: the node's own position and neighbour columns, or
   // for a radial wall lane (WL kernels, wl = +-1, node (j, k) being its
@@ -1062,25 +1332,25 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   if (MODE != MODE_FIELDS) {
     // ---- source (Eq. 24) and relaxation (Eq. 21) --------------------------
     float S1, S7, S8;
-    source(D.src_printed != 0, rho, ur, uz, iphi, Fr, Fz, ar, S1, S7, S8);
+    source<EX>(D.src_printed != 0, rho, ur, uz, iphi, Fr, Fz, ar, S1, S7, S8);
     const float S5 = rho * Fz;
     // The radial-momentum and radial-flux increments are written so that the
     // quiescent parts (c_s^2 / (2 r) in n_3, n_4 and c_s^2 / r in S_3) and
     // the change of reference state (-c_s^2 / r in moment 3, +c_s^2 / r in
     // moment 4) cancel exactly: what remains scales with rho - 1 and u.
-    const float S3d = rho * (Fr - R.ar1 * ur);  // S_3 minus its quiescent part rho c_s^2 / r
-    const float X3 = -D.s_j * (Jr - rho * ur) + (1.0f - 0.5f * D.s_j) * S3d +
-                     (2.0f - D.s_j) * R.hcs2r * B.drho;
-    const float X4 = -D.s_q * (m4 + rho * ur) - (1.0f - 0.5f * D.s_q) * S3d -
-                     (2.0f - D.s_q) * R.hcs2r * B.drho;
-    float X[8] = {-D.s_e * B.n1 + (1.0f - 0.5f * D.s_e) * S1,
-                  -D.s_eps * B.n2 - (1.0f - 0.5f * D.s_eps) * S1,
+    const float S3d = rho * (Fr - (EX ? mul_rounded(R.ar1, ur) : R.ar1 * ur));  // S_3 minus its quiescent part rho c_s^2 / r
+    const float X3 = add_product<EX>(sum_second<EX>(-D.s_j, sub_product<EX>(Jr, rho, ur), 1.0f - 0.5f * D.s_j, S3d),
+                                     (2.0f - D.s_j) * R.hcs2r, B.drho);
+    const float X4 = sub_product<EX>(diff_first<EX>(-D.s_q, add_product<EX>(m4, rho, ur), 1.0f - 0.5f * D.s_q, S3d),
+                                     (2.0f - D.s_q) * R.hcs2r, B.drho);
+    float X[8] = {sum_second<EX>(-D.s_e, B.n1, 1.0f - 0.5f * D.s_e, S1),
+                  diff_first<EX>(-D.s_eps, B.n2, 1.0f - 0.5f * D.s_eps, S1),
                   X3,
                   X4,
-                  -D.s_j * B.n5 + (1.0f - 0.5f * D.s_j) * S5,
-                  -D.s_q * B.n6 - (1.0f - 0.5f * D.s_q) * S5,
-                  -D.s_nu * B.n7 + (1.0f - 0.5f * D.s_nu) * S7,
-                  -D.s_nu * B.n8 + (1.0f - 0.5f * D.s_nu) * S8};
+                  sum_second<EX>(-D.s_j, B.n5, 1.0f - 0.5f * D.s_j, S5),
+                  diff_first<EX>(-D.s_q, B.n6, 1.0f - 0.5f * D.s_q, S5),
+                  sum_second<EX>(-D.s_nu, B.n7, 1.0f - 0.5f * D.s_nu, S7),
+                  sum_second<EX>(-D.s_nu, B.n8, 1.0f - 0.5f * D.s_nu, S8)};
 
     // ---- temperature collision (Eqs. 33-37) ------------------------------
     // q_i = g_i - wt_i T is the part of g - g^eq that does not depend on u;
@@ -1092,14 +1362,23 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
     float tg[5];
     {
       const float e1 = 5.0f * ur, e2 = 5.0f * uz;
-      const float q1 = t[1] - WT1 * B.theta, q2 = t[2] - WT1 * B.theta;
-      const float q3 = t[3] - WT1 * B.theta, q4 = t[4] - WT1 * B.theta;
+      const float q1 = thermal_neq<EX, false>(t[1], B.theta), q2 = thermal_neq<EX, WL>(t[2], B.theta);
+      const float q3 = thermal_neq<EX, false>(t[3], B.theta), q4 = thermal_neq<EX, WL>(t[4], B.theta);
       const float q0 = -((q1 + q3) + (q2 + q4));
-      tg[0] = t[0] - D.omc * q0 + psi * wT0;
-      tg[1] = t[1] - R.omT1 * (q1 - wT1 * e1) + psi * wT1 * (1.0f + e1);
-      tg[2] = t[2] - D.omc * (q2 - wT1 * e2) + psi * wT1 * (1.0f + e2);
-      tg[3] = t[3] - R.omT3 * (q3 + wT1 * e1) + psi * wT1 * (1.0f - e1);
-      tg[4] = t[4] - D.omc * (q4 + wT1 * e2) + psi * wT1 * (1.0f - e2);
+      if constexpr (EX) {
+        const float pw = mul_rounded(psi, wT1);
+        tg[0] = ffma(psi, wT0, ffma(-D.omc, q0, t[0]));
+        tg[1] = ffma(ffma(5.0f, ur, 1.0f), pw, ffma(-R.omT1, ffma(-wT1, e1, q1), t[1]));
+        tg[2] = ffma(ffma(5.0f, uz, 1.0f), pw, ffma(-D.omc, ffma(-wT1, e2, q2), t[2]));
+        tg[3] = ffma(ffma(-5.0f, ur, 1.0f), pw, ffma(-R.omT3, ffma(wT1, e1, q3), t[3]));
+        tg[4] = ffma(ffma(-5.0f, uz, 1.0f), pw, ffma(-D.omc, ffma(wT1, e2, q4), t[4]));
+      } else {
+        tg[0] = t[0] - D.omc * q0 + psi * wT0;
+        tg[1] = t[1] - R.omT1 * (q1 - wT1 * e1) + psi * wT1 * (1.0f + e1);
+        tg[2] = t[2] - D.omc * (q2 - wT1 * e2) + psi * wT1 * (1.0f + e2);
+        tg[3] = t[3] - R.omT3 * (q3 + wT1 * e1) + psi * wT1 * (1.0f - e1);
+        tg[4] = t[4] - D.omc * (q4 + wT1 * e2) + psi * wT1 * (1.0f - e2);
+      }
     }
     for (int q = 0; q < 5; ++q) B.t[q] = t[q];
 
@@ -1121,7 +1400,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
 #if defined(__HIP_DEVICE_COMPILE__)
         if constexpr (sizeof(S) == 2) asm volatile("" : "+v"(rw), "+v"(wlw));
 #endif
-        wall_lane_inputs(D, B, t, rw, wlw, k, row0 + jw, dw, Xw, ga, Tb);
+        wall_lane_inputs<EX, sizeof(S) == 2>(D, B, t, rw, wlw, k, plane_index<BUF>(D, row0 + jw), dw, Xw, ga, Tb);
 #pragma unroll
         for (int i = 0; i < 9; ++i) d[i] = isw ? dw[i] : d[i];
 #pragma unroll
@@ -1142,7 +1421,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
     }
 
     // ---- back-transform (Eq. 22) ------------------------------------------
-    back_transform(d, X[0], X[1], X[2], X[3], X[4], X[5], X[6], X[7]);
+    back_transform<EX>(d, X[0], X[1], X[2], X[3], X[4], X[5], X[6], X[7]);
 
     // ---- stream and store --------------------------------------------------
     if constexpr (sizeof(S) == 4) {
@@ -1156,7 +1435,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
         P.st(8, os, d[6], rn.next());
         P.st(5, os, d[7], rn.next());
         P.st(6, os, d[8], rn.next());
-        D.g0[os] = tg[0];
+        D.g0[plane_index<BUF>(D, os)] = tg[0];
         P.st(12, os, tg[1], rn.next());
         P.st(13, os, tg[2], rn.next());
         P.st(10, os, tg[3], rn.next());
@@ -1172,7 +1451,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
         P.st(R.mir ? 5 : 6, rowp + cm, d[6], rn.next());
         P.st(R.mir ? 8 : 7, rowm + cm, d[7], rn.next());
         P.st(8, rowm + cp, d[8], rn.next());
-        D.g0[os] = tg[0];
+        D.g0[plane_index<BUF>(D, os)] = tg[0];
         P.st(10, row0 + cp, tg[1], rn.next());
         P.st(11, rowp + js, tg[2], rn.next());
         P.st(R.mir ? 10 : 12, row0 + cm, tg[3], rn.next());
@@ -1206,7 +1485,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
         P.st(R.mir ? 8 : 7, rowm + cm, d[7], r[7]);
         P.st(8, rowm + cp, d[8], r[8]);
       }
-      D.g0[os] = tg[0];
+      D.g0[plane_index<BUF>(D, os)] = tg[0];
     }
   } else {
     for (int q = 0; q < 5; ++q) B.t[q] = t[q];
@@ -1217,6 +1496,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   if constexpr (WL && MODE != MODE_FIELDS) {
     if (wl != 0) return;  // a wall lane's wall node is stored above
   }
+  if constexpr (MODE == MODE_TILE) return;
   const bool own_rm = D.side_rmin == SIDE_WALL && j == 1;
   const bool own_rp = D.side_rmax == SIDE_WALL && j == D.nr - 2;
   const bool own_zm = z_bounded(D) && k == 1;
@@ -1251,7 +1531,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
 }
 
 // One fluid node (j, k) at one time step (load, then update).
-template <typename S, bool ODD, int MODE, bool BUF = false, bool WL = false>
+template <typename S, bool ODD, int MODE, int BUF = ADDR_FLAT, bool WL = false>
 __host__ __device__ inline void node_update(const InstDev& D, const RowC& R, int j, int k,
                                             int mac_slot, const FieldOut& fo, uint32_t seed,
                                             int wl = 0) {

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include "lbm_axi_dev.h"
+#include "lbm_axi_tile.h"
 
 namespace lbmaxi {
 
@@ -224,12 +225,27 @@ hipError_t launch_init_t(const StepLaunch& L, const float* dinit, float T_init, 
   return hipGetLastError();
 }
 
+// nsteps steps from level t on a list of tiles (k_tile).
+struct TileLaunch {
+  const InstDev *src, *dst;
+  const StepTile* tiles;
+  const int* status;
+  int ntiles, nf, nt, lds_bytes;  // nf: fluid threads of the nt of a block
+  hipStream_t stream;
+};
+template <typename S>
+hipError_t launch_tile_t(const TileLaunch& L, int nsteps, long long t) {
+  k_tile<S><<<L.ntiles, L.nt, L.lds_bytes, L.stream>>>(L.src, L.dst, L.tiles, L.status, TILE_VWLOG, L.nf, nsteps, t);
+  return hipGetLastError();
+}
+
 // FP16 / BF16 launches (lbm_axi_s16.hip); storage is LBM_STORE_FP16 or
 // LBM_STORE_BF16.  Each returns the launch's hipError_t.
 hipError_t launch_step_s16(int storage, bool buf, bool wall_lanes, bool odd, int mode, const StepLaunch& L,
                            int mac_slot, uint32_t seed, const long long* clk, int off);
 hipError_t launch_fields_s16(int storage, bool odd, const StepLaunch& L, const FieldOut& fo);
 hipError_t launch_pattern_s16(int storage, bool buf, bool odd, const StepLaunch& L, uint32_t key);
+hipError_t launch_tile_s16(int storage, const TileLaunch& L, int nsteps, long long t);
 hipError_t launch_init_s16(int storage, const StepLaunch& L, const float* dinit, float T_init, int inst);
 
 }  // namespace lbmaxi
