@@ -76,7 +76,8 @@ struct DevResult {
 };
 
 struct ResTile {
-  int inst, k0, k1, pad;
+  int inst, k0, k1;
+  int cols;  // log2 of the threads along a row; the block's others take the next rows
 };
 
 // Scratch of lbm_axi_stream_function_static, for callers that cannot
@@ -215,6 +216,10 @@ __device__ inline double wave_sum(double v) {
 
 // FP64 partial sums over fluid nodes of the rows [k0, k1) of one instance:
 // |du|^2, node count, dT^2, |u|^2, and the Eq. (42) integrands on both walls.
+// A thread's nodes are a serial chain of loads (about 1 us each on a grid that
+// fills no cache line twice), so the handle is cut into about 2048 blocks (eight
+// for each compute unit) of 512 to 8192 nodes, and on short rows a block takes
+// several at once.
 __global__ __launch_bounds__(RB) void k_resid(const InstDev* __restrict__ descs,
                                               const ResTile* __restrict__ rts, int cur,
                                               const int* __restrict__ status,
@@ -226,9 +231,10 @@ __global__ __launch_bounds__(RB) void k_resid(const InstDev* __restrict__ descs,
   const float* pv = cur ? D.mac[0] : D.mac[1];
   const int64_t pl = D.plane;
   double a[6] = {0, 0, 0, 0, 0, 0};
-  for (int k = rt.k0; k < rt.k1; ++k) {
+  const int nc = 1 << rt.cols, jt = threadIdx.x & (nc - 1);
+  for (int k = rt.k0 + (int)(threadIdx.x >> rt.cols); k < rt.k1; k += RB >> rt.cols) {
     const double ck = (k == 0 || k == D.nz - 1) ? 0.5 : 1.0;
-    for (int j = threadIdx.x; j < D.nr; j += RB) {
+    for (int j = jt; j < D.nr; j += nc) {
       const int64_t o = (int64_t)k * D.stride + j;
       if (!is_boundary(D, j, k)) {
         const double uz = cu[o], ur = cu[pl + o], T = cu[2 * pl + o];
@@ -1165,17 +1171,24 @@ int lbm_axi_create(const lbm_axi_params* p, int32_t n_inst, const float* const* 
       }
       HIPBAIL(hipMemcpy(h->dres, r0.data(), sizeof(DevResult) * n_inst, hipMemcpyHostToDevice));
     }
-    // Reduction tiles: RZ rows per block.
+    // Reduction tiles: rows of about a 2048th of the handle's nodes (k_resid).
     if (h->check > 0) {
       std::vector<ResTile> rts;
+      int64_t nodes = 0;
+      for (int i = 0; i < n_inst; ++i) nodes += (int64_t)p[i].nr * p[i].nz;
+      const int64_t per_block = std::min<int64_t>(8192, std::max<int64_t>(512, nodes / 2048));
       std::vector<int> first(2 * n_inst);
       std::vector<double> tol(n_inst), tail(n_inst), nus(4 * n_inst);
       std::vector<long long> mx(n_inst);
       for (int i = 0; i < n_inst; ++i) {
         const int nz = p[i].nz, nr = p[i].nr;
-        int rz = std::max(1, (int)((8192 + nr - 1) / nr));  // about 8k nodes per block
+        int cols = 3;
+        while (cols < 8 && (1 << cols) < nr) ++cols;
+        const int ty = RB >> cols;
+        const int64_t rz = std::max<int64_t>(1, (per_block / nr + ty - 1) / ty) * ty;
         first[2 * i] = (int)rts.size();
-        for (int k0 = 0; k0 < nz; k0 += rz) rts.push_back(ResTile{i, k0, std::min(nz, k0 + rz), 0});
+        for (int64_t k0 = 0; k0 < nz; k0 += rz)
+          rts.push_back(ResTile{i, (int)k0, (int)std::min<int64_t>(nz, k0 + rz), cols});
         first[2 * i + 1] = (int)rts.size() - first[2 * i];
         tol[i] = p[i].tol;
         tail[i] = p[i].tail_tol;
