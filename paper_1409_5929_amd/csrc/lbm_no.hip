@@ -54,8 +54,7 @@ __host__ __device__ inline bf16_t to_bf16(float v) {  // round to nearest even (
 }
 
 constexpr int NT = 256;      // threads of a GEMM block (four waves)
-constexpr int GBK = 64;      // k per LDS stage of the GEMM
-constexpr int GLD = GBK + 8; // padded LDS row (bf16): 144 B, rows stay 16-byte aligned
+constexpr int GBK = 64;      // weight-gradient splits are multiples of this many k
 constexpr int EW = 256;      // threads of the elementwise kernels
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -83,8 +82,8 @@ __device__ inline uint32_t word(const uint4& v, int d) { return d == 0 ? v.x : d
 // A is k-contiguous (row m at A + m lda).  BKC: B(k, n) = B[n ldb + k];
 // otherwise B(k, n) = B[k ldb + n].  Split z covers k in [z kchunk,
 // (z + 1) kchunk) and writes C + z cz.
-// Block: WM x (4 / WM) waves, each 64 x 64 outputs as 4 x 4 MFMA tiles of
-// 16 x 16; k staged through LDS 64 at a time with k contiguous (B
+// Block: WM x (4 / WM) waves, each TM x TN MFMA tiles of 16 x 16 outputs
+// (gemm_shape); k staged through LDS 256 / TN at a time with k contiguous (B
 // transposed on the way when n-contiguous: each thread turns a 4 (k) x 8 (n)
 // block around in registers and writes eight 8-byte rows).  The next stage's
 // operands are loaded into registers while the current one is multiplied.
@@ -106,41 +105,44 @@ struct PhaseT {
   int K[4], base[4], run[4], gap[4];
   int Hn, Wn;
 };
-template <bool BKC, int WM, bool PH, bool PAIR>
+template <bool BKC, int WM, bool PH, bool PAIR, int TM, int TN>
 __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* __restrict__ A,
                                              int64_t lda, int vecA, const bf16_t* __restrict__ B,
                                              int64_t ldb, int vecB, float* __restrict__ C, int64_t ldc,
                                              int64_t cz, int kchunk, const float* __restrict__ bias,
                                              int accumulate, PhaseT ph, int relu) {
+  static_assert(TN == 4 || TN == TM, "stages are 256 / TN long");
   static_assert(!(PH && BKC) && (PH || !PAIR), "phase GEMMs take an n-contiguous B");
-  constexpr int WN = 4 / WM, TBM = 64 * WM, TBN = 64 * WN;
-  constexpr int NA = TBM * GBK / 8 / NT;   // 16-byte A chunks per thread and stage
-  constexpr int NB = TBN * GBK / 8 / NT;   // 16-byte B chunks per thread and stage
+  constexpr int WN = 4 / WM, TBM = 16 * TM * WM, TBN = 16 * TN * WN;
+  constexpr int GBK = 256 / TN;            // k per LDS stage
+  constexpr int GLD = GBK + 8;             // padded LDS row (bf16): 4 banks on from the last, 16-byte aligned
+  constexpr int CA = TBM * GBK / 8, NA = (CA + NT - 1) / NT;  // 16-byte A chunks per stage and per thread
+  constexpr int NB = TBN * GBK / 8 / NT;  // 16-byte B chunks per thread and stage
   __shared__ __attribute__((aligned(16))) bf16_t As[TBM * GLD];
   __shared__ __attribute__((aligned(16))) bf16_t Bs[TBN * GLD];
   const int m0 = blockIdx.y * TBM, n0 = blockIdx.x * TBN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave / WN) * 64, wn = (wave % WN) * 64;
+  const int wm = (wave / WN) * 16 * TM, wn = (wave % WN) * 16 * TN;
   uint4 ra[NA], rb[NB];
   // acc += A B over k in [kb, ke) (phase q: A + ph.aoff[q], B rows mapped)
-  auto mainloop = [&](const int q, const int kb, const int ke, v4f (&acc)[4][4]) {
+  auto mainloop = [&](const int q, const int kb, const int ke, v4f (&acc)[TM][TN]) {
     const bf16_t* __restrict__ Aq = PH ? A + ph.aoff[q] : A;
     auto load = [&](int k0) {
 #pragma unroll
       for (int it = 0; it < NA; ++it) {
-        const int e = tid + it * NT, r = e >> 3, c = (e & 7) << 3;
-        ra[it] = m0 + r < M ? load8(Aq + (int64_t)(m0 + r) * lda, k0 + c, ke, vecA) : make_uint4(0u, 0u, 0u, 0u);
+        const int e = tid + it * NT, r = e / (GBK / 8), c = (e % (GBK / 8)) * 8;
+        ra[it] = m0 + r < M && (CA % NT == 0 || e < CA) ? load8(Aq + (int64_t)(m0 + r) * lda, k0 + c, ke, vecA) : make_uint4(0u, 0u, 0u, 0u);
       }
       if constexpr (BKC) {
 #pragma unroll
         for (int it = 0; it < NB; ++it) {
-          const int e = tid + it * NT, r = e >> 3, c = (e & 7) << 3;
+          const int e = tid + it * NT, r = e / (GBK / 8), c = (e % (GBK / 8)) * 8;
           rb[it] = n0 + r < N ? load8(B + (int64_t)(n0 + r) * ldb, k0 + c, ke, vecB) : make_uint4(0u, 0u, 0u, 0u);
         }
-      } else {  // blocks of 4 k x 8 n: k = 4 (e % 16) + r, n = 8 (e / 16) + 0..7
+      } else {  // blocks of 4 k x 8 n
 #pragma unroll
         for (int it = 0; it < NB / 4; ++it) {
-          const int e = tid + it * NT, kq = (e & 15) << 2, n8 = (e >> 4) << 3;
+          const int e = tid + it * NT, kq = (e % (GBK / 4)) * 4, n8 = e / (GBK / 4) * 8;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int gk = k0 + kq + r;
@@ -153,19 +155,19 @@ __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* 
     auto stash = [&]() {
 #pragma unroll
       for (int it = 0; it < NA; ++it) {
-        const int e = tid + it * NT, r = e >> 3, c = (e & 7) << 3;
-        *(uint4*)&As[r * GLD + c] = ra[it];
+        const int e = tid + it * NT, r = e / (GBK / 8), c = (e % (GBK / 8)) * 8;
+        if (CA % NT == 0 || e < CA) *(uint4*)&As[r * GLD + c] = ra[it];
       }
       if constexpr (BKC) {
 #pragma unroll
         for (int it = 0; it < NB; ++it) {
-          const int e = tid + it * NT, r = e >> 3, c = (e & 7) << 3;
+          const int e = tid + it * NT, r = e / (GBK / 8), c = (e % (GBK / 8)) * 8;
           *(uint4*)&Bs[r * GLD + c] = rb[it];
         }
       } else {
 #pragma unroll
         for (int it = 0; it < NB / 4; ++it) {
-          const int e = tid + it * NT, kq = (e & 15) << 2, n8 = (e >> 4) << 3;
+          const int e = tid + it * NT, kq = (e % (GBK / 4)) * 4, n8 = e / (GBK / 4) * 8;
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             const int d = i >> 1, h = i & 1;
@@ -178,9 +180,9 @@ __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* 
       }
     };
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int j = 0; j < TN; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     if (kb < ke) load(kb);
     for (int k0 = kb; k0 < ke; k0 += GBK) {
       __syncthreads();  // the previous stage's fragments are read
@@ -190,17 +192,17 @@ __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* 
 #pragma unroll
       for (int kk = 0; kk < GBK; kk += 32) {
         const int kq = kk + 8 * (lane >> 4);
-        v8bf a[4], b[4];
+        v8bf a[TM], b[TN];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TM; ++i)
           a[i] = __builtin_bit_cast(v8bf, *(const uint4*)&As[(wm + i * 16 + (lane & 15)) * GLD + kq]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < TN; ++j)
           b[j] = __builtin_bit_cast(v8bf, *(const uint4*)&Bs[(wn + j * 16 + (lane & 15)) * GLD + kq]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
+          for (int j = 0; j < TN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
       }
     }
@@ -209,12 +211,12 @@ __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* 
   if constexpr (!PAIR) {
     const int q = PH ? (int)blockIdx.z : 0;
     const int kb = PH ? 0 : (int)blockIdx.z * kchunk, ke = PH ? ph.K[q] : min(K, kb + kchunk);
-    v4f acc[4][4];
+    v4f acc[TM][TN];
     mainloop(q, kb, ke, acc);
     float* Cz = C + (PH ? 0 : (int64_t)blockIdx.z * cz);
-    int64_t cof[4];  // column offsets in a row of C
+    int64_t cof[TN];  // column offsets in a row of C
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < TN; ++j) {
       const int gn = n0 + wn + j * 16 + (lane & 15);
       cof[j] = gn;
       if (PH) {
@@ -224,14 +226,14 @@ __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* 
       }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int gm = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
         if (gm >= M) continue;
         const float bv = (bias && (PH || blockIdx.z == 0)) ? bias[gm] : 0.0f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < TN; ++j) {
           const int gn = n0 + wn + j * 16 + (lane & 15);
           if (gn < N) {
             float* c = Cz + (int64_t)gm * ldc + cof[j];
@@ -244,27 +246,27 @@ __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* 
     // block z = py: both column phases px = 0, 1 of the row phase, so each
     // output (b, 2y + py, 2x .. 2x + 1) is one 8-byte store
     const int py = (int)blockIdx.z;
-    v4f acc0[4][4], acc1[4][4];
+    v4f acc0[TM][TN], acc1[TM][TN];
     mainloop(2 * py, 0, ph.K[2 * py], acc0);
     __syncthreads();  // LDS reused by the second phase
     mainloop(2 * py + 1, 0, ph.K[2 * py + 1], acc1);
-    int64_t cof[4];  // offset of (b, 2y + py, 2x) in a row of C
+    int64_t cof[TN];  // offset of (b, 2y + py, 2x) in a row of C
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < TN; ++j) {
       const int gn = n0 + wn + j * 16 + (lane & 15);
       const int hw = ph.Hn * ph.Wn;
       const int b = gn / hw, r = gn - b * hw, y = r / ph.Wn, x = r - y * ph.Wn;
       cof[j] = ((int64_t)b * 2 * ph.Hn + 2 * y + py) * (2 * ph.Wn) + 2 * x;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int gm = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
         if (gm >= M) continue;
         const float bv = bias ? bias[gm] : 0.0f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < TN; ++j) {
           const int gn = n0 + wn + j * 16 + (lane & 15);
           if (gn < N) {
             float2* c = (float2*)(C + (int64_t)gm * ldc + cof[j]);
@@ -706,10 +708,30 @@ namespace {
 // (256 compute units), each split a multiple of GBK long; the partial sums
 // are added in split order.
 constexpr int SPLIT_BLOCKS = 512;
-// GEMM block shape: 64 x 256 outputs for M <= 64 (wm = 1), else 128 x 128.
-int gemm_wm(int64_t M) { return M <= 64 ? 1 : 2; }
+// GEMM block shape (k_gemm): wm waves along M with tm x tn MFMA tiles each.
+struct GemmShape {
+  int wm, tm, tn;
+  int bm() const { return 16 * tm * wm; }
+  int bn() const { return 16 * tn * (4 / wm); }
+  int64_t rows(int64_t M) const { return (M + bm() - 1) / bm(); }
+  int64_t tiles(int64_t M, int64_t N) const { return rows(M) * ((N + bn() - 1) / bn()); }
+};
+// A block's k stages are a serial chain of about 1.5 us each (load, LDS, MFMA),
+// so a GEMM that leaves compute units idle takes smaller blocks with longer
+// stages: large ones (64 x 256 outputs for M <= 64, else 128 x 128, or 48 and
+// 96 rows where M pads to less) from 512 blocks on, then 64 x 64 ones from 256
+// blocks on, else 32 x 32.  Measured, 128^2 forward of widths from 48: batch 1
+// 265 us with large blocks alone, 160 with 64 x 64 ones, 128 with all three;
+// batch 8 389, 316 and 312.  Every shape adds the products of an output in the
+// same order.
+GemmShape gemm_shape(int64_t M, int64_t N, int64_t nz) {
+  const GemmShape g4{M <= 64 ? 1 : 2, 4, 4}, g3{g4.wm, 3, 4}, g2{2, 2, 2};
+  const GemmShape g = g3.rows(M) * g3.bm() < g4.rows(M) * g4.bm() ? g3 : g4;
+  if (g.tiles(M, N) * nz >= 512) return g;
+  return g2.tiles(M, N) * nz >= 256 ? g2 : GemmShape{2, 1, 1};
+}
 void wgrad_split(int64_t M, int64_t N, int64_t P, int& S, int64_t& kchunk) {
-  const int64_t bm = 64 * gemm_wm(M), bn = 256 / gemm_wm(M);
+  const int64_t wm = M <= 64 ? 1 : 2, bm = 64 * wm, bn = 256 / wm;
   const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   int64_t s = std::max<int64_t>(1, (SPLIT_BLOCKS + tiles - 1) / tiles);
   s = std::min<int64_t>(s, (P + GBK - 1) / GBK);
@@ -758,15 +780,17 @@ int gemm(lbm_no* h, int M, int N, int K, const bf16_t* A, int64_t lda, const bf1
     return fail(LBM_NO_EINVAL, "GEMM operand shapes");
   auto aligned = [](const void* p, int64_t ld) { return ((uintptr_t)p & 15) == 0 && ld % 8 == 0; };
   const int vecA = aligned(A, lda) && kchunk % 8 == 0, vecB = aligned(B, ldb) && (!BKC || kchunk % 8 == 0);
-  const int wm = gemm_wm(M), bm = 64 * wm, bn = 256 / wm;
-  const dim3 grid((unsigned)((N + bn - 1) / bn), (unsigned)((M + bm - 1) / bm), (unsigned)splits);
+  const GemmShape g = gemm_shape(M, N, splits);
+  const dim3 grid((unsigned)((N + g.bn() - 1) / g.bn()), (unsigned)g.rows(M), (unsigned)splits);
   const PhaseT ph{};
-  if (wm == 1)
-    k_gemm<BKC, 1, false, false><<<grid, NT, 0, h->stream>>>(M, N, K, A, lda, vecA, B, ldb, vecB, C, ldc, cz,
-                                                             kchunk, bias, accumulate, ph, relu);
-  else
-    k_gemm<BKC, 2, false, false><<<grid, NT, 0, h->stream>>>(M, N, K, A, lda, vecA, B, ldb, vecB, C, ldc, cz,
-                                                             kchunk, bias, accumulate, ph, relu);
+#define LBM_NO_G(WMV, TMV, TNV)                                                                                     \
+  k_gemm<BKC, WMV, false, false, TMV, TNV><<<grid, NT, 0, h->stream>>>(M, N, K, A, lda, vecA, B, ldb, vecB, C, ldc, \
+                                                                       cz, kchunk, bias, accumulate, ph, relu)
+  if (g.tm == 1) LBM_NO_G(2, 1, 1);
+  else if (g.tm == 2) LBM_NO_G(2, 2, 2);
+  else if (g.tm == 3) { if (g.wm == 1) LBM_NO_G(1, 3, 4); else LBM_NO_G(2, 3, 4); }
+  else { if (g.wm == 1) LBM_NO_G(1, 4, 4); else LBM_NO_G(2, 4, 4); }
+#undef LBM_NO_G
   NOCHK(hipGetLastError());
   return LBM_NO_OK;
 }
@@ -782,20 +806,21 @@ int gemm_phases(lbm_no* h, int M, int N, const bf16_t* A, int64_t lda, const bf1
       return fail(LBM_NO_EINVAL, "phase GEMM operand shapes");
   auto aligned = [](const void* p, int64_t ld) { return ((uintptr_t)p & 15) == 0 && ld % 8 == 0; };
   const int vecA = aligned(A, lda), vecB = aligned(B, ldb);
-  const int wm = gemm_wm(M), bm = 64 * wm, bn = 256 / wm;
-  const unsigned tiles = (unsigned)(((N + bn - 1) / bn) * ((M + bm - 1) / bm));
+  const GemmShape g = gemm_shape(M, N, 4);
   // both column phases per block (contiguous output pairs) when that still
   // gives at least two blocks per compute unit
-  const bool pair = 2 * tiles >= 512 && ((uintptr_t)C & 7) == 0 && (ldc & 1) == 0;
-  const dim3 grid((unsigned)((N + bn - 1) / bn), (unsigned)((M + bm - 1) / bm), pair ? 2u : 4u);
-#define LBM_NO_PH(WMV, PAIRV)                                                                                  \
-  k_gemm<false, WMV, true, PAIRV><<<grid, NT, 0, h->stream>>>(M, N, 0, A, lda, vecA, B, ldb, vecB, C, ldc, 0, 0, \
-                                                              bias, accumulate, ph, relu)
-  if (wm == 1) {
-    if (pair) LBM_NO_PH(1, true); else LBM_NO_PH(1, false);
-  } else {
-    if (pair) LBM_NO_PH(2, true); else LBM_NO_PH(2, false);
-  }
+  const bool pair = g.tm > 1 && 2 * g.tiles(M, N) >= 512 && ((uintptr_t)C & 7) == 0 && (ldc & 1) == 0;
+  const dim3 grid((unsigned)((N + g.bn() - 1) / g.bn()), (unsigned)g.rows(M), pair ? 2u : 4u);
+#define LBM_NO_PH1(WMV, PAIRV, TMV, TNV)                                                                        \
+  k_gemm<false, WMV, true, PAIRV, TMV, TNV><<<grid, NT, 0, h->stream>>>(M, N, 0, A, lda, vecA, B, ldb, vecB, C, \
+                                                                        ldc, 0, 0, bias, accumulate, ph, relu)
+#define LBM_NO_PH(WMV, TMV, TNV) \
+  if (pair) LBM_NO_PH1(WMV, true, TMV, TNV); else LBM_NO_PH1(WMV, false, TMV, TNV)
+  if (g.tm == 1) LBM_NO_PH1(2, false, 1, 1);
+  else if (g.tm == 2) { LBM_NO_PH(2, 2, 2); }
+  else if (g.tm == 3) { if (g.wm == 1) { LBM_NO_PH(1, 3, 4); } else { LBM_NO_PH(2, 3, 4); } }
+  else { if (g.wm == 1) { LBM_NO_PH(1, 4, 4); } else { LBM_NO_PH(2, 4, 4); } }
+#undef LBM_NO_PH1
 #undef LBM_NO_PH
   NOCHK(hipGetLastError());
   return LBM_NO_OK;
