@@ -763,6 +763,8 @@ void release(lbm_axi* h, void* p, size_t bytes) {
 
 // ---- steps on LDS tiles (k_tile) ----
 
+constexpr int TILE_CUS = 256;  // compute units
+
 void drop_tile_plan(lbm_axi* h) {
   if (h->dsteptiles) (void)hipFree(h->dsteptiles);
   h->dsteptiles = nullptr;
@@ -788,8 +790,7 @@ std::vector<StepTile> step_tiles(const lbm_axi* h, bool live, int& walls, size_t
         out.push_back(StepTile{i, cj[b], cj[b + 1], ck[a], ck[a + 1], 0, 0, 0});
         const TileRegion g = tile_load_region(D, out.back(), h->tile_m);
         const size_t n = (size_t)(g.kh - g.kl) * TILE_VW;
-        lds = std::max(lds, h->storage == LBM_STORE_FP32 ? tile_bytes<float>(D.phi_mode != 0, n)
-                                                         : tile_bytes<__half>(D.phi_mode != 0, n));
+        lds = std::max(lds, h->storage == LBM_STORE_FP32 ? tile_bytes<float>(n) : tile_bytes<__half>(n));
         walls = std::max(walls, tile_walls<true>(D, g).count);
       }
   }
@@ -805,6 +806,8 @@ bool build_step_tiles(lbm_axi* h) {
   h->tile_nf = TILE_NT - (walls + 63) / 64 * 64;
   h->tile_lds = (int)lds;
   if (h->tile_nf < TILE_NT / 2 || lds > (size_t)h->lds_per_block) return false;
+  for (const StepTile& T : live)
+    if (!tile_inside(h->hdesc[T.inst], T, h->tile_m)) return false;
   const int T = (int)live.size(), per = T > 0 ? (T + 7) / 8 : 1;
   std::vector<StepTile> order((size_t)per * 8, StepTile{-1, 0, 0, 0, 0, 0, 0, 0});
   for (int b = 0; b < per * 8; ++b)
@@ -824,12 +827,16 @@ bool build_step_tiles(lbm_axi* h) {
 // Whether the handle's plain steps run on LDS tiles, and with which shape.
 // Steps per launch and rows per tile: while one tile per compute unit covers
 // the handle, long runs (8 steps) on the shortest tiles that still fit the 256
-// units; above that a launch is bound by its vector work, and the halo, worked on
-// again by each tile, is kept small: 6, then 4 steps on tiles of 28 rows.
+// units; above that a launch is bound by its vector
+// work, and the halo, worked on again by each tile, is kept small: 6, then 4 steps
+// on tiles of about 28 rows, two at a time on a unit (34 rows fill half its
+// LDS).  A few such rounds of tiles: as many rows as save a round, no more (64 of
+// 128^2: 20.8 us with 26 rows in 4 rounds, 18.7 with 32 in 3; 1000^2: 17.8 with 28
+// and 18.1 with 34, both 3).
 // Measured, us per step in single steps and on tiles: FP32 pipe 64 x 8 4.1 and
-// 1.8, annulus 100 x 200 7.2 and 2.9, 300^2 8.0 and 4.2, 632^2 14.1 and 10.3, 64
-// of 128^2 30.6 and 21.9, 1500 x 4000 154 and 110, the 1024 grids of the sweep
-// 1786 and 1319; FP16 200^2 9.0 and 6.3, 512^2 11.9 and 10.1.  In 16-bit storage
+// 1.7, annulus 100 x 200 7.2 and 2.6, 300^2 8.0 and 4.1, 512^2 11.1 and 6.8, 64
+// of 128^2 30.6 and 18.7, 1000^2 26.5 and 17.8, the first 256 grids of the sweep
+// 449 and 302; FP16 200^2 9.0 and 5.6, 512^2 11.9 and 9.3.  In 16-bit storage
 // single steps take over where the tiles come to more than one for each compute
 // unit (550^2: 13.1 and 14.4, four of 300^2 12.2 and 14.7): they move half the
 // bytes, and the halo's roundings cost more.
@@ -854,12 +861,30 @@ void plan_tiles(lbm_axi* h) {
   size_t free_b = 0, total = 0;
   if (hipMemGetInfo(&free_b, &total) != hipSuccess || bytes > total / 16 || bytes > free_b / 4) return;
   h->tile_m = nodes <= 1e5 ? 8 : (nodes <= 4e5 ? 6 : 4);
-  h->tile_h = 28;
-  if (nodes <= 1e5) {
+  for (const InstDev& D : h->hdesc) h->tile_m = std::min(h->tile_m, tile_max_steps(D));
+  auto tiles = [&](int rows) {
     int walls;
     size_t lds;
-    for (h->tile_h = 5; h->tile_h < 28; ++h->tile_h)
-      if (step_tiles(h, false, walls, lds).size() <= 256) break;
+    h->tile_h = rows;
+    return (int64_t)step_tiles(h, false, walls, lds).size();
+  };
+  if (nodes <= 1e5) {
+    for (int rows = 5; rows <= 28; ++rows)
+      if (tiles(rows) <= TILE_CUS) break;
+  } else if (nodes <= 4e5) {
+    h->tile_h = 28;
+  } else {
+    int best = 30;
+    const int64_t round = 2 * TILE_CUS;
+    int64_t least = (tiles(best) + round - 1) / round;
+    if (least <= 8) {
+      least = INT64_MAX;
+      for (int rows = 34; rows >= 26; rows -= 2) {
+        const int64_t r = (tiles(rows) + round - 1) / round;
+        if (r <= least) least = r, best = rows;
+      }
+    }
+    h->tile_h = best;
   }
   std::vector<InstDev> b(h->hdesc);
   hipError_t err = hipSuccess;

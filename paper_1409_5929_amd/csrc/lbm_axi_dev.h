@@ -245,11 +245,29 @@ __device__ inline void unpack(uint32_t w, float inv, float& f, float& g) {
 
 template <typename S, int BUF>
 struct PopAcc;
-// Index of node offset o in the planes a descriptor points to: a tile's planes
-// start at its first node.
-template <int BUF>
+// Product of two numbers in [0, 2^24) below 2^31: one full-rate instruction
+// (a 32-bit product takes four times as long).
+__host__ __device__ inline int mul24(int a, int b) {
+  return (int)(((uint32_t)a & 0xFFFFFFu) * ((uint32_t)b & 0xFFFFFFu));
+}
+// A node in LDS (ADDR_TILE) holds all it has in consecutive words, so that one
+// address serves its loads and stores with immediate offsets.  FP32: slots 0..13
+// (g_0 is slot 9) and the porosity; 16-bit storage: the five single slots as
+// halves, the four pair words, FP32 g_0 and the porosity.  An odd number of words: consecutive
+// nodes lie in different banks.
+template <typename S>
+struct TileNode {
+  static constexpr int WORDS = sizeof(S) == 4 ? 15 : 9, G0 = sizeof(S) == 4 ? 9 : 7, PHI = WORDS - 1, PAIR = 3;
+  // element of slot q (q = 9: FP32 only) in elements of S
+  __host__ __device__ static constexpr int slot(int q) {
+    if (sizeof(S) == 4) return q;
+    return q == 0 ? 0 : q <= 4 ? 2 * (PAIR + q - 1) : q <= 8 ? q - 4 : 2 * (PAIR + q - 10) + 1;
+  }
+};
+// Index of node offset o in the g_0 and porosity planes that a descriptor points to.
+template <int BUF, typename S>
 __host__ __device__ inline int64_t plane_index(const InstDev& D, int64_t o) {
-  if constexpr (BUF == ADDR_TILE) return o - D.t_base;
+  if constexpr (BUF == ADDR_TILE) return mul24((int)o - D.t_base, TileNode<S>::WORDS);
   return o;
 }
 template <typename S>
@@ -360,19 +378,40 @@ struct PopAcc<S, ADDR_BUF> {
   }
 };
 
-// PopAcc<S, ADDR_TILE>: a tile's populations in LDS, through a tile descriptor
-// (tile_desc).  32-bit indices; same layout and roundings as the planes in HBM.
+// PopAcc<S, ADDR_TILE>: a tile's populations in LDS (TileNode), through a tile
+// descriptor (tile_desc).  32-bit indices; same values and roundings as in HBM.
 template <typename S>
 struct PopAcc<S, ADDR_TILE> {
   static constexpr int ADDR = ADDR_TILE;
-  PopAcc<S, ADDR_FLAT> A;
+  using N = TileNode<S>;
+  S* P;
   int base;
-  __host__ __device__ explicit PopAcc(const InstDev& D) : A(D), base(D.t_base) {}
-  __host__ __device__ float ld(int q, int64_t o) const { return A.ld(q, (int)o - base); }
-  __host__ __device__ void st(int q, int64_t o, float v, uint32_t r) const { A.st(q, (int)o - base, v, r); }
-  __host__ __device__ void ld_pair(int a, int64_t o, float& f, float& g) const { A.ld_pair(a, (int)o - base, f, g); }
+  float inv, sc;
+  __host__ __device__ explicit PopAcc(const InstDev& D) : P((S*)D.pop), base(D.t_base), inv(D.st_inv), sc(D.st_scale) {}
+  __host__ __device__ int at(int64_t o) const { return mul24((int)o - base, N::WORDS * 4 / (int)sizeof(S)); }
+  __host__ __device__ float ld(int q, int64_t o) const { return Store<S>::ld(P, at(o) + N::slot(q), inv); }
+  __host__ __device__ void st(int q, int64_t o, float v, uint32_t r) const {
+    Store<S>::st_sr(P, at(o) + N::slot(q), v, sc, r);
+  }
+  __host__ __device__ void ld_pair(int a, int64_t o, float& f, float& g) const {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (sizeof(S) == 2) {
+      unpack<S>(((const uint32_t*)P)[mul24((int)o - base, N::WORDS) + N::PAIR + a], inv, f, g);
+      return;
+    }
+#endif
+    f = ld(a + 1, o);
+    g = ld(a + 10, o);
+  }
   __host__ __device__ void st_pair(int a, int64_t o, float f, float g, uint32_t rf, uint32_t rg) const {
-    A.st_pair(a, (int)o - base, f, g, rf, rg);
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (sizeof(S) == 2) {
+      ((uint32_t*)P)[mul24((int)o - base, N::WORDS) + N::PAIR + a] = pack_sr<S>(f * sc, g * sc, rf, rg);
+      return;
+    }
+#endif
+    st(a + 1, o, f, rf);
+    st(a + 10, o, g, rg);
   }
 };
 
@@ -396,7 +435,11 @@ struct Dither {
 };
 
 // Offset of row k in a plane (64-bit: planes of large grids pass 2^31).
-__host__ __device__ inline int64_t row_off(int k, int stride) { return (int64_t)k * stride; }
+template <int BUF = ADDR_FLAT>
+__host__ __device__ inline int64_t row_off(int k, int stride) {
+  if constexpr (BUF == ADDR_TILE) return mul24(k, stride);
+  return (int64_t)k * stride;
+}
 
 // Identity of node (j, k), offset o, in the random stream: its offset in the
 // instance's planes.  Where a tile descriptor's rows are unwrapped (tile_desc)
@@ -765,7 +808,7 @@ __host__ __device__ inline void wall_node(const InstDev& D, const A& P, const No
   const float inv_rb = frcp(rb);
   const int64_t ob = row_off(kb, D.stride) + jb;
   float phib, cDb, cFb;
-  porosity_of(D, D.phi_mode == 0 ? 0.0f : D.phi[plane_index<A::ADDR>(D, ob)], phib, cDb, cFb);
+  porosity_of(D, D.phi_mode == 0 ? 0.0f : D.phi[plane_index<A::ADDR, S>(D, ob)], phib, cDb, cFb);
   const uint8_t m = node_mask(D, jb, kb);
   float drho = B.drho, urb = 0.0f, uzb = 0.0f;
   const bool moving = D.side_z == SIDE_FLOW && !(m & (MASK_RMIN | MASK_RMAX));  // inlet or outlet
@@ -883,7 +926,7 @@ __host__ __device__ inline void wall_node_alone(const InstDev& D, const A& P, co
   const float inv_rb = frcp(rb);
   const int64_t ob = row_off(kb, D.stride) + jb;
   float phib, cDb, cFb;
-  porosity_of(D, D.phi_mode == 0 ? 0.0f : D.phi[plane_index<A::ADDR>(D, ob)], phib, cDb, cFb);
+  porosity_of(D, D.phi_mode == 0 ? 0.0f : D.phi[plane_index<A::ADDR, S>(D, ob)], phib, cDb, cFb);
   const uint8_t m = node_mask(D, jb, kb);
   float drho = B.drho, urb = 0.0f, uzb = 0.0f;
   const bool moving = D.side_z == SIDE_FLOW && !(m & (MASK_RMIN | MASK_RMAX));
@@ -983,13 +1026,13 @@ __host__ __device__ inline void node_load(const InstDev& D, const RowC& R, int j
     if (km < 0) km += D.nz;
     if (kp >= D.nz) kp -= D.nz;
   }
-  const int64_t rowm = row_off(km, st), row0 = row_off(k, st), rowp = row_off(kp, st);
+  const int64_t rowm = row_off<BUF>(km, st), row0 = row_off<BUF>(k, st), rowp = row_off<BUF>(kp, st);
   const int64_t o = row0 + j;
   if constexpr (sizeof(S) == 4) {
     if (!ODD) {
 #pragma unroll
       for (int q = 0; q < 9; ++q) s[q] = P.ld(q, o);
-      t[0] = D.g0[plane_index<BUF>(D, o)];
+      t[0] = D.g0[plane_index<BUF, S>(D, o)];
 #pragma unroll
       for (int q = 1; q < 5; ++q) t[q] = P.ld(9 + q, o);
     } else {
@@ -1003,7 +1046,7 @@ __host__ __device__ inline void node_load(const InstDev& D, const RowC& R, int j
       s[6] = P.ld(8, rowm + cp);
       s[7] = P.ld(5, rowp + cp);
       s[8] = P.ld(R.mir ? 5 : 6, rowp + cm);
-      t[0] = D.g0[plane_index<BUF>(D, o)];
+      t[0] = D.g0[plane_index<BUF, S>(D, o)];
       t[1] = P.ld(R.mir ? 10 : 12, row0 + cm);
       t[2] = P.ld(13, rowm + j);
       t[3] = P.ld(10, row0 + cp);
@@ -1017,7 +1060,7 @@ __host__ __device__ inline void node_load(const InstDev& D, const RowC& R, int j
       for (int a = 0; a < 4; ++a) P.ld_pair(a, o, s[a + 1], t[a + 1]);
 #pragma unroll
       for (int q = 5; q < 9; ++q) s[q] = P.ld(q, o);
-      t[0] = D.g0[plane_index<BUF>(D, o)];
+      t[0] = D.g0[plane_index<BUF, S>(D, o)];
     } else {
       const int64_t cm = R.cm, cp = R.cp;
       s[0] = P.ld(0, o);
@@ -1029,10 +1072,10 @@ __host__ __device__ inline void node_load(const InstDev& D, const RowC& R, int j
       s[6] = P.ld(8, rowm + cp);
       s[7] = P.ld(5, rowp + cp);
       s[8] = P.ld(R.mir ? 5 : 6, rowp + cm);
-      t[0] = D.g0[plane_index<BUF>(D, o)];
+      t[0] = D.g0[plane_index<BUF, S>(D, o)];
     }
   }
-  phi_raw = D.phi_mode == 0 ? 0.0f : D.phi[plane_index<BUF>(D, o)];
+  phi_raw = D.phi_mode == 0 ? 0.0f : D.phi[plane_index<BUF, S>(D, o)];
 }
 
 // Slots of the populations arriving at fluid node (j, k) in the AA layout of
@@ -1228,7 +1271,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
     if (km < 0) km += D.nz;
     if (kp >= D.nz) kp -= D.nz;
   }
-  const int64_t rowm = row_off(km, st), row0 = row_off(k, st), rowp = row_off(kp, st);
+  const int64_t rowm = row_off<BUF>(km, st), row0 = row_off<BUF>(k, st), rowp = row_off<BUF>(kp, st);
   const int64_t o = row0 + j;
   Dither rn(mix32(seed ^ dither_id<BUF>(D, o, j, k, wl)));  // a wall lane draws its wall node's stream
   float t[5] = {t_in[0], t_in[1], t_in[2], t_in[3], t_in[4]};
@@ -1400,7 +1443,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
 #if defined(__HIP_DEVICE_COMPILE__)
         if constexpr (sizeof(S) == 2) asm volatile("" : "+v"(rw), "+v"(wlw));
 #endif
-        wall_lane_inputs<EX, sizeof(S) == 2>(D, B, t, rw, wlw, k, plane_index<BUF>(D, row0 + jw), dw, Xw, ga, Tb);
+        wall_lane_inputs<EX, sizeof(S) == 2>(D, B, t, rw, wlw, k, plane_index<BUF, S>(D, row0 + jw), dw, Xw, ga, Tb);
 #pragma unroll
         for (int i = 0; i < 9; ++i) d[i] = isw ? dw[i] : d[i];
 #pragma unroll
@@ -1435,7 +1478,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
         P.st(8, os, d[6], rn.next());
         P.st(5, os, d[7], rn.next());
         P.st(6, os, d[8], rn.next());
-        D.g0[plane_index<BUF>(D, os)] = tg[0];
+        D.g0[plane_index<BUF, S>(D, os)] = tg[0];
         P.st(12, os, tg[1], rn.next());
         P.st(13, os, tg[2], rn.next());
         P.st(10, os, tg[3], rn.next());
@@ -1451,7 +1494,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
         P.st(R.mir ? 5 : 6, rowp + cm, d[6], rn.next());
         P.st(R.mir ? 8 : 7, rowm + cm, d[7], rn.next());
         P.st(8, rowm + cp, d[8], rn.next());
-        D.g0[plane_index<BUF>(D, os)] = tg[0];
+        D.g0[plane_index<BUF, S>(D, os)] = tg[0];
         P.st(10, row0 + cp, tg[1], rn.next());
         P.st(11, rowp + js, tg[2], rn.next());
         P.st(R.mir ? 10 : 12, row0 + cm, tg[3], rn.next());
@@ -1485,7 +1528,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
         P.st(R.mir ? 8 : 7, rowm + cm, d[7], r[7]);
         P.st(8, rowm + cp, d[8], r[8]);
       }
-      D.g0[plane_index<BUF>(D, os)] = tg[0];
+      D.g0[plane_index<BUF, S>(D, os)] = tg[0];
     }
   } else {
     for (int q = 0; q < 5; ++q) B.t[q] = t[q];

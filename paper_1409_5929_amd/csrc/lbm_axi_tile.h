@@ -6,7 +6,9 @@
 // about 5 us a step, however few nodes there are.  Here one block takes a tile
 // of the grid through an even number m of steps: it copies the tile's
 // populations, with a halo of m nodes, from the planes into LDS (same slots,
-// same storage type), runs the step's own node code on the LDS copy in place
+// same storage type, all of a node in consecutive words: with a plane for each
+// slot, as in HBM, every access formed its own address, 35 of a node's 360 vector
+// instructions), runs the step's own node code on the LDS copy in place
 // (the AA pattern needs one barrier per step), on a region that shrinks by one
 // node per step towards the tile, and copies the tile's slots to a second set
 // of planes.  Tiles overlap only where they read, so blocks never wait for
@@ -61,6 +63,18 @@ __host__ __device__ inline TileRegion tile_load_region(const InstDev& D, const S
   return g;
 }
 
+// The most steps per launch that an instance takes: an unwrapped region reaches m
+// rows beyond its tile, and no row may be more than one period away (tile_row).
+inline int tile_max_steps(const InstDev& D) { return D.side_z == SIDE_PERIODIC ? D.nz & ~1 : 1 << 20; }
+
+// Whether a tile's region for m steps lies in the rows and columns that stand for
+// the instance's nodes: what k_tile reads then lies in the instance's planes.
+inline bool tile_inside(const InstDev& D, const StepTile& T, int m) {
+  const TileRegion g = tile_load_region(D, T, m);
+  return g.jl >= 0 && g.jh <= D.nr && g.kl >= 0 && g.kh <= (tile_unwrapped(D, T) ? 3 * D.nz : D.nz) && T.j0 >= g.jl &&
+         T.j1 <= g.jh;
+}
+
 // Cuts of an instance into tiles for m steps, so that a tile's region is at most vw
 // columns wide: columns cj[i] .. cj[i + 1], rows ck[i] .. ck[i + 1] of about h.
 // Tiles at either radial side need no halo there and are wider by m.
@@ -78,11 +92,10 @@ inline void tile_cuts(const InstDev& D, int vw, int m, int h, std::vector<int>& 
   for (int i = 0; i <= nk; ++i) ck.push_back((int)((int64_t)D.nz * i / nk));
 }
 
-// LDS bytes of a tile of n nodes: 14 planes of the storage type (13 and an FP32
-// g_0 in 16-bit storage) and the porosity field, if any.
+// LDS bytes of n nodes.
 template <typename S>
-__host__ __device__ inline size_t tile_bytes(bool field, size_t n) {
-  return n * ((sizeof(S) == 4 ? 56 : 30) + (field ? 4 : 0));
+__host__ __device__ inline size_t tile_bytes(size_t n) {
+  return n * (4 * TileNode<S>::WORDS);
 }
 
 // Descriptor of region g held at lds in rows of vw nodes: the instance's, with
@@ -99,8 +112,8 @@ __host__ __device__ inline InstDev tile_desc(const InstDev& D, const StepTile& T
   L.t_base = g.kl * vw + g.jl;
   L.t_stride = D.stride;
   L.pop = lds;
-  L.g0 = sizeof(S) == 4 ? (float*)lds + 9 * n : (float*)(lds + 26 * (size_t)n);
-  L.phi = (const float*)(lds + (size_t)n * (sizeof(S) == 4 ? 56 : 30));
+  L.g0 = (float*)lds + TileNode<S>::G0;
+  L.phi = (const float*)lds + TileNode<S>::PHI;
   if (D.side_rmin == SIDE_WALL && g.jl == 1) L.side_rmin = SIDE_PERIODIC;
   if (D.side_rmax == SIDE_WALL && g.jh == D.nr - 1) L.side_rmax = SIDE_PERIODIC;
   if (tile_unwrapped(D, T)) {
@@ -127,32 +140,45 @@ __host__ __device__ inline bool tile_lane(const InstDev& D, int j, int& wl) {
   return WL && (wl > 0 || wall_lane_rmax(D));
 }
 
-// Copies the slots of one node, at offset o of planes of pl nodes (16-bit
-// storage: single planes and pair words, see slot_elem).
+// The slots and porosity of the node at offset o of an instance's planes to
+// its words in LDS (TileNode), and the slots back.
 template <typename S>
-__host__ __device__ inline void tile_copy(const void* src, const float* sg, int64_t so, int64_t spl, void* dst,
-                                          float* dg, int64_t dof, int64_t dpl) {
+__host__ __device__ inline void tile_in(const InstDev& D, int64_t o, uint32_t* n) {
+  using N = TileNode<S>;
   if constexpr (sizeof(S) == 4) {
-    (void)sg;
-    (void)dg;
     float v[14];
 #pragma unroll
-    for (int q = 0; q < 14; ++q) v[q] = ((const float*)src)[q * spl + so];
+    for (int q = 0; q < 14; ++q) v[q] = ((const float*)D.pop)[q * D.plane + o];
 #pragma unroll
-    for (int q = 0; q < 14; ++q) ((float*)dst)[q * dpl + dof] = v[q];
+    for (int q = 0; q < 14; ++q) ((float*)n)[q] = v[q];
   } else {
     uint16_t v[5];
     uint32_t w[4];
 #pragma unroll
-    for (int q = 0; q < 5; ++q) v[q] = ((const uint16_t*)src)[q * spl + so];
+    for (int q = 0; q < 5; ++q) v[q] = ((const uint16_t*)D.pop)[q * D.plane + o];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) w[a] = ((const uint32_t*)src)[(5 + 2 * a) * (spl >> 1) + so];
-    const float g = sg[so];
+    for (int a = 0; a < 4; ++a) w[a] = ((const uint32_t*)D.pop)[(5 + 2 * a) * (D.plane >> 1) + o];
+    const float g = D.g0[o];
 #pragma unroll
-    for (int q = 0; q < 5; ++q) ((uint16_t*)dst)[q * dpl + dof] = v[q];
+    for (int q = 0; q < 5; ++q) ((uint16_t*)n)[q] = v[q];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) ((uint32_t*)dst)[(5 + 2 * a) * (dpl >> 1) + dof] = w[a];
-    dg[dof] = g;
+    for (int a = 0; a < 4; ++a) n[N::PAIR + a] = w[a];
+    ((float*)n)[N::G0] = g;
+  }
+  if (D.phi_mode) ((float*)n)[N::PHI] = D.phi[o];
+}
+template <typename S>
+__host__ __device__ inline void tile_out(const uint32_t* n, const InstDev& D, void* pop, float* g0, int64_t o) {
+  using N = TileNode<S>;
+  if constexpr (sizeof(S) == 4) {
+#pragma unroll
+    for (int q = 0; q < 14; ++q) ((float*)pop)[q * D.plane + o] = ((const float*)n)[q];
+  } else {
+#pragma unroll
+    for (int q = 0; q < 5; ++q) ((uint16_t*)pop)[q * D.plane + o] = ((const uint16_t*)n)[q];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) ((uint32_t*)pop)[(5 + 2 * a) * (D.plane >> 1) + o] = n[N::PAIR + a];
+    g0[o] = ((const float*)n)[N::G0];
   }
 }
 
@@ -233,19 +259,17 @@ __global__ __launch_bounds__(TILE_NT) __attribute__((amdgpu_waves_per_eu(4))) vo
   if (T.inst < 0 || status[T.inst] != RUN) return;
   const InstDev D = src[T.inst];
   constexpr bool WL = true;
-  // vwlog = TILE_VWLOG as an argument: with the constant the compiler hoists 24
-  // registers more out of the step loop than it has, and spills them
+  // vwlog = TILE_VWLOG as an argument: with the constant the compiler hoists ten
+  // more registers out of the step loop (FP32, 64 of 128^2: 18.6 and 18.2 us)
   const int vw = 1 << vwlog, c = (int)threadIdx.x & (vw - 1), rg = (int)threadIdx.x >> vwlog;
   const int RB = (int)blockDim.x >> vwlog, RG = nf >> vwlog;
   const TileRegion g = tile_load_region(D, T, nsteps);
   const InstDev L = tile_desc<S>(D, T, g, vw, tile_lds);
+  uint32_t* lds = (uint32_t*)tile_lds;
   int j = g.jl + c;
   if (j < g.jh)
     for (int k = g.kl + rg; k < g.kh; k += RB) {
-      const int64_t o = row_off(tile_row(D, T, k), D.stride) + j;
-      const int l = (k - g.kl) * vw + c;
-      tile_copy<S>(D.pop, D.g0, o, D.plane, L.pop, L.g0, l, L.plane);
-      if (D.phi_mode) ((float*)L.phi)[l] = D.phi[o];
+      tile_in<S>(D, row_off(tile_row(D, T, k), D.stride) + j, lds + mul24(((k - g.kl) << vwlog) + c, TileNode<S>::WORDS));
     }
   const FieldOut fo{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   const TileWalls w = tile_walls<WL>(D, g);
@@ -296,8 +320,8 @@ __global__ __launch_bounds__(TILE_NT) __attribute__((amdgpu_waves_per_eu(4))) vo
     for (int k = g.kl + rg; k < g.kh; k += RB) {
       const int kt = tile_unwrapped(D, T) ? k - D.nz : k;
       if (kt < T.k0 || kt >= T.k1) continue;
-      tile_copy<S>(L.pop, L.g0, (k - g.kl) * vw + c, L.plane, O->pop, O->g0,
-                   row_off(tile_row(D, T, k), D.stride) + j, D.plane);
+      tile_out<S>(lds + mul24(((k - g.kl) << vwlog) + c, TileNode<S>::WORDS), D, O->pop, O->g0,
+                  row_off(tile_row(D, T, k), D.stride) + j);
     }
 }
 

@@ -56,15 +56,13 @@ CASES = {
 
 
 @pytest.mark.parametrize("storage", ["fp32", "fp16"])
-@pytest.mark.parametrize("shape", [(2, 16, 5), (4, 16, 8), (4, 64, 7), (8, 32, 30)], ids=str)
+@pytest.mark.parametrize("shape", [(2, 16, 5), (4, 16, 8), (4, 64, 7), (8, 32, 30), (10, 32, 12)], ids=str)
 @pytest.mark.parametrize("name", CASES)
 def test_tiles_equal_single_steps(host, name, shape, storage):
     from paper_1409_5929_amd import lbm
 
     cfg, field = CASES[name]
     m, vw, h = shape
-    if m > cfg["nz"]:
-        pytest.skip("the library takes at most nz steps per launch")
     phi = np.ascontiguousarray(li.porosity_grf(cfg["nz"], cfg["nr"], seed=5), np.float32) if field else None
     init = np.ascontiguousarray(_init(cfg, 1409), np.float32)
     p = lbm.make_params(cfg, storage=storage, check_interval=0)
@@ -75,3 +73,17 @@ def test_tiles_equal_single_steps(host, name, shape, storage):
         assert rc == 0, f"host_tile_steps returned {rc}"
         assert np.isfinite(b).all()
         np.testing.assert_array_equal(a, b, err_msg=f"{name}, wall lanes {wall_lanes}")
+
+
+@pytest.mark.parametrize("nz", [8, 9, 11, 12, 40])
+def test_periodic_rows_bound_the_steps_per_launch(host, nz):
+    """A tile of a short periodic grid that takes more steps than the grid has
+    rows would read rows that stand for none."""
+    from paper_1409_5929_amd import lbm
+
+    p = lbm.make_params(li.pipe(nr=40, nz=nz), storage="fp32", check_interval=0)
+    most = ctypes.c_int()
+    for m in range(2, 13, 2):
+        inside = host.host_tile_inside(ctypes.byref(p), m, 32, 5, ctypes.byref(most))
+        assert most.value == nz // 2 * 2
+        assert inside == (1 if m <= nz else 0)

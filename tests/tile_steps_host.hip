@@ -50,17 +50,16 @@ template <typename S, bool WL>
 bool tile_block(const InstDev& D, const InstDev& O, const StepTile& T, int vw, int nsteps, long long t) {
   const size_t GUARD = 4096;
   const TileRegion g = tile_load_region(D, T, nsteps);
+  if (!tile_inside(D, T, nsteps)) return false;
   if (g.jh - g.jl > vw) return false;
-  const size_t bytes = tile_bytes<S>(D.phi_mode != 0, (size_t)vw * (g.kh - g.kl));
+  const size_t bytes = tile_bytes<S>((size_t)vw * (g.kh - g.kl));
   std::vector<unsigned char> mem(bytes + 2 * GUARD, 0xFF);  // NaN wherever nothing was written
   unsigned char* lds = mem.data() + GUARD;
   const InstDev L = tile_desc<S>(D, T, g, vw, lds);
   for (int k = g.kl; k < g.kh; ++k)
     for (int j = g.jl; j < g.jh; ++j) {
-      const int64_t o = row_off(tile_row(D, T, k), D.stride) + j;
-      const int l = (k - g.kl) * vw + j - g.jl;
-      tile_copy<S>(D.pop, D.g0, o, D.plane, L.pop, L.g0, l, L.plane);
-      if (D.phi_mode) ((float*)L.phi)[l] = D.phi[o];
+      tile_in<S>(D, row_off(tile_row(D, T, k), D.stride) + j,
+                 (uint32_t*)lds + ((k - g.kl) * vw + j - g.jl) * TileNode<S>::WORDS);
     }
   for (int i = 0; i < nsteps; ++i) {
     const TileRegion a = tile_region(D, T, nsteps - i);
@@ -91,8 +90,8 @@ bool tile_block(const InstDev& D, const InstDev& O, const StepTile& T, int vw, i
     const int kt = tile_unwrapped(D, T) ? k - D.nz : k;
     if (kt < T.k0 || kt >= T.k1) continue;
     for (int j = T.j0; j < T.j1; ++j)
-      tile_copy<S>(L.pop, L.g0, (k - g.kl) * vw + j - g.jl, L.plane, O.pop, O.g0,
-                   row_off(tile_row(D, T, k), D.stride) + j, D.plane);
+      tile_out<S>((uint32_t*)lds + ((k - g.kl) * vw + j - g.jl) * TileNode<S>::WORDS, D, O.pop, O.g0,
+                  row_off(tile_row(D, T, k), D.stride) + j);
   }
   for (size_t b = 0; b < GUARD; ++b)
     if (mem[b] != 0xFF || mem[GUARD + bytes + b] != 0xFF) return false;
@@ -130,6 +129,7 @@ int run(const lbm_axi_params* p, const float* phi_field, const float* init, int 
         init_node<S>(I[q], j, k, init[o], init[n + o], init[2 * n + o]);
       }
   std::vector<int> cj, ck;
+  m = std::min(m, tile_max_steps(D));
   tile_cuts(D, vw, m, h, cj, ck);
   int cur = 0;
   for (int t = 0; t < nsteps;) {
@@ -172,4 +172,18 @@ extern "C" int host_tile_steps(const lbm_axi_params* p, const float* phi_field, 
                       : run<float, false>(p, phi_field, init, nsteps, m, vw, h, tiled, single);
   return wall_lanes ? run<__half, true>(p, phi_field, init, nsteps, m, vw, h, tiled, single)
                     : run<__half, false>(p, phi_field, init, nsteps, m, vw, h, tiled, single);
+}
+
+// Whether every tile of about h rows may take m steps (tile_inside), and the most steps.
+extern "C" int host_tile_inside(const lbm_axi_params* p, int m, int vw, int h, int* most) {
+  InstDev D;
+  std::string err;
+  if (describe(*p, false, D, err)) return -1;
+  *most = tile_max_steps(D);
+  std::vector<int> cj, ck;
+  tile_cuts(D, vw, m, h, cj, ck);
+  for (size_t a = 0; a + 1 < ck.size(); ++a)
+    for (size_t b = 0; b + 1 < cj.size(); ++b)
+      if (!tile_inside(D, StepTile{0, cj[b], cj[b + 1], ck[a], ck[a + 1], 0, 0, 0}, m)) return 0;
+  return 1;
 }
