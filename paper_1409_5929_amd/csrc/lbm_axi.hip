@@ -138,6 +138,7 @@ struct lbm_axi {
   std::vector<char> active;     // instances in the launch list (empty: all)
   bool buf = false;             // step kernels use buffer addressing (all arrays below 4 GiB)
   bool wall_lanes = false;      // step kernels compute radial wall nodes on their own lanes
+  int wall_mode = -1;           // as lbm_axi_set_wall_lanes set it
   long long* dclk = nullptr;    // device clock of captured step graphs
   int graph_steps = 32;         // steps per captured graph (0: no graphs)
   // steps on LDS tiles (k_tile): 0 not planned yet, 1 planned, -1 not used
@@ -840,11 +841,15 @@ bool build_step_tiles(lbm_axi* h) {
 // single steps take over where the tiles come to more than one for each compute
 // unit (550^2: 13.1 and 14.4, four of 300^2 12.2 and 14.7): they move half the
 // bytes, and the halo's roundings cost more.
-// Only handles with wall lanes take tiles: the tile kernel's radial walls are
-// theirs, bit for bit.
+// The tile kernel's radial walls are those of the step kernels with wall lanes,
+// bit for bit.  Handles without them by default (rows of more than 2560 columns)
+// take tiles in FP32, where the two differ by rounding: 8192^2 runs 1414 us a step
+// in single steps and 1026 on tiles.  In 16-bit storage, whose stochastic rounding would
+// turn that into other bits, and where the caller has switched wall lanes
+// off, they do not.
 void plan_tiles(lbm_axi* h) {
   h->tile_plan = -1;
-  if (!h->wall_lanes) return;
+  if (!h->wall_lanes && (h->wall_mode == 0 || h->storage != LBM_STORE_FP32)) return;
   const size_t esz = h->storage == LBM_STORE_FP32 ? 4 : 2;
   size_t bytes = 0;
   double nodes = 0.0;
@@ -852,7 +857,7 @@ void plan_tiles(lbm_axi* h) {
     const bool flux = D.therm_rmin == THERM_FLUX || D.therm_rmax == THERM_FLUX;
     // radially periodic columns wrap across tiles; the heated window of a flux wall is tested on unwrapped rows
     if (D.side_rmin == SIDE_PERIODIC || (D.side_z == SIDE_PERIODIC && (flux || D.nz < 8))) return;
-    if (D.nr < 4 || D.nz < 4) return;
+    if (D.nr < 4 || D.nz < 4 || D.nz > 5000000) return;  // row numbers of a tile: below 2^24 (mul24)
     bytes += (size_t)D.plane * (14 * esz + (esz == 2 ? 4 : 0));
     nodes += (double)D.nr * D.nz;
   }
@@ -1525,10 +1530,9 @@ int lbm_axi_set_wall_lanes(lbm_axi* h, int32_t mode, int32_t* on) {
     if (!h || mode < -1 || mode > 1) return fail(LBM_AXI_EINVAL, "bad handle or mode not in {-1, 0, 1}");
     HIPCHK(hipStreamSynchronize(h->stream));
     const bool want = mode < 0 ? default_wall_lanes(h) : mode == 1;
-    if (want != h->wall_lanes) {
-      drop_graph(h);  // captured graphs hold the other kernels
-      drop_tile_plan(h);
-    }
+    if (want != h->wall_lanes) drop_graph(h);  // captured graphs hold the other kernels
+    if (want != h->wall_lanes || mode != h->wall_mode) drop_tile_plan(h);
+    h->wall_mode = mode;
     h->wall_lanes = want;
     if (on) *on = want ? 1 : 0;
     return LBM_AXI_OK;

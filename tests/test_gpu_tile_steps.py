@@ -83,3 +83,25 @@ def test_tiles_follow_compaction_and_storage_conversion(L):  # noqa: F811
         same(run.fields(i), one.fields(i), f"instance {i}")
     run.close()
     one.close()
+
+
+@pytest.mark.parametrize("nr,nz", [(2600, 40), (3001, 33)])
+def test_wide_grids_take_tiles_within_rounding(L, nr, nz):  # noqa: F811
+    """Rows of more than 2560 columns: single steps leave the radial walls to their
+    owners, tiles give them lanes.  The two differ by FP32 rounding (2e-6 of a
+    field's norm, the bound between the two kernels of single steps), and a
+    handle whose wall lanes are switched off takes single steps only."""
+    c = li.annulus(nr=nr, nz=nz, Ra=1e5, Da=1e-3)
+    init = [_init(c, 5)]
+    got = []
+    for mode, timed in ((-1, False), (-1, True), (0, False)):
+        lat = L.Lattice([c], init=init, check_interval=0)
+        lat.set_wall_lanes(mode)
+        lat.set_timing(timed)
+        lat.step(60)
+        got.append(lat.fields(0))
+        lat.close()
+    same(got[1], got[2], "without wall lanes")
+    for k in ("uz", "ur", "T"):
+        a, b = got[0][k].astype(np.float64), got[1][k].astype(np.float64)
+        assert np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b), k
