@@ -100,10 +100,21 @@ __device__ inline uint32_t word(const uint4& v, int d) { return d == 0 ? v.x : d
 // aligned base, kchunk a multiple of 8), so whole 8-element chunks move as
 // one 16-byte load; otherwise element by element.  Zero outside the
 // matrices.
+// SKIP (phase GEMMs): C = max(C, 0) + skip, skip laid out like C; where not null,
+// a16 gets C in bfloat16 (the operand of a following 1 x 1 layer) and mask a byte
+// for each output, nonzero where it was positive before the skip (the
+// backward's relu mask).  A pass of its own for this read and wrote 12 bytes an
+// output.
+struct SkipT {
+  const float* skip;
+  bf16_t* a16;
+  uint8_t* mask;
+};
 struct PhaseT {
   int64_t aoff[4];
   int K[4], base[4], run[4], gap[4];
   int Hn, Wn;
+  SkipT sk;
 };
 template <bool BKC, int WM, bool PH, bool PAIR, int TM, int TN>
 __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* __restrict__ A,
@@ -225,23 +236,41 @@ __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* 
         cof[j] = ((int64_t)b * 2 * ph.Hn + 2 * y + (q >> 1)) * (2 * ph.Wn) + 2 * x + (q & 1);
       }
     }
+    // what is added to an output (C itself or the skip input) is loaded for a
+    // whole tile before its stores, which the loads could not pass
+    const float* add = accumulate ? Cz : (PH ? ph.sk.skip : nullptr);
+    const bool skip = PH && ph.sk.skip != nullptr;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+      const int gm0 = m0 + wm + i * 16 + 4 * (lane >> 4);
+      float pre[4][TN];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          pre[r][j] = add && gm0 + r < M && n0 + wn + j * 16 + (lane & 15) < N ? add[(int64_t)(gm0 + r) * ldc + cof[j]] : 0.0f;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int gm = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
+        const int gm = gm0 + r;
         if (gm >= M) continue;
         const float bv = (bias && (PH || blockIdx.z == 0)) ? bias[gm] : 0.0f;
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           const int gn = n0 + wn + j * 16 + (lane & 15);
-          if (gn < N) {
-            float* c = Cz + (int64_t)gm * ldc + cof[j];
-            const float v = (accumulate ? *c : 0.0f) + (acc[i][j][r] + bv);
-            *c = relu ? fmaxf(v, 0.0f) : v;
+          if (gn >= N) continue;
+          const int64_t at = (int64_t)gm * ldc + cof[j];
+          const float v = (skip ? 0.0f : pre[r][j]) + (acc[i][j][r] + bv);
+          if (skip) {
+            const float w = fmaxf(v, 0.0f) + pre[r][j];
+            Cz[at] = w;
+            if (ph.sk.a16) ph.sk.a16[at] = to_bf16(w);
+            if (ph.sk.mask) ph.sk.mask[at] = v > 0.0f;
+          } else {
+            Cz[at] = relu ? fmaxf(v, 0.0f) : v;
           }
         }
       }
+    }
   } else {
     // block z = py: both column phases px = 0, 1 of the row phase, so each
     // output (b, 2y + py, 2x .. 2x + 1) is one 8-byte store
@@ -258,26 +287,43 @@ __global__ __launch_bounds__(NT) void k_gemm(int M, int N, int K, const bf16_t* 
       const int b = gn / hw, r = gn - b * hw, y = r / ph.Wn, x = r - y * ph.Wn;
       cof[j] = ((int64_t)b * 2 * ph.Hn + 2 * y + py) * (2 * ph.Wn) + 2 * x;
     }
+    const float* add = accumulate ? C : ph.sk.skip;
+    const bool skip = ph.sk.skip != nullptr;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+      const int gm0 = m0 + wm + i * 16 + 4 * (lane >> 4);
+      float2 pre[4][TN];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          pre[r][j] = add && gm0 + r < M && n0 + wn + j * 16 + (lane & 15) < N
+                          ? *(const float2*)(add + (int64_t)(gm0 + r) * ldc + cof[j])
+                          : make_float2(0.0f, 0.0f);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int gm = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
+        const int gm = gm0 + r;
         if (gm >= M) continue;
         const float bv = bias ? bias[gm] : 0.0f;
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           const int gn = n0 + wn + j * 16 + (lane & 15);
-          if (gn < N) {
-            float2* c = (float2*)(C + (int64_t)gm * ldc + cof[j]);
-            float2 v = accumulate ? *c : make_float2(0.0f, 0.0f);
-            v.x += acc0[i][j][r] + bv;
-            v.y += acc1[i][j][r] + bv;
-            if (relu) v = make_float2(fmaxf(v.x, 0.0f), fmaxf(v.y, 0.0f));
-            *c = v;
+          if (gn >= N) continue;
+          const int64_t at = (int64_t)gm * ldc + cof[j];
+          float2 v = skip ? make_float2(0.0f, 0.0f) : pre[r][j];
+          v.x += acc0[i][j][r] + bv;
+          v.y += acc1[i][j][r] + bv;
+          if (skip) {
+            if (ph.sk.mask) *(uint16_t*)(ph.sk.mask + at) = (uint16_t)((v.x > 0.0f ? 1 : 0) | (v.y > 0.0f ? 256 : 0));
+            v = make_float2(fmaxf(v.x, 0.0f) + pre[r][j].x, fmaxf(v.y, 0.0f) + pre[r][j].y);
+            if (ph.sk.a16) *(uint32_t*)(ph.sk.a16 + at) = (uint32_t)to_bf16(v.x) | (uint32_t)to_bf16(v.y) << 16;
+          } else if (relu) {
+            v = make_float2(fmaxf(v.x, 0.0f), fmaxf(v.y, 0.0f));
           }
+          *(float2*)(C + at) = v;
         }
       }
+    }
   }
 }
 
@@ -341,32 +387,15 @@ __device__ inline float block_sum(float v, float* sh) {
   return t;
 }
 
-// a = relu(z) (or z) + skip; and a in bfloat16 into a16 (may be null): the
-// im2col of a following 1 x 1 layer, whose rows are a's channels.
-__global__ __launch_bounds__(EW) void k_act(const float* __restrict__ z, const float* __restrict__ skip,
-                                            float* __restrict__ a, int64_t n, int relu,
-                                            bf16_t* __restrict__ a16) {
-  const int64_t i = (int64_t)blockIdx.x * EW + threadIdx.x;
-  if (i >= n) return;
-  float v = z[i];
-  if (relu) v = fmaxf(v, 0.0f);
-  v = skip ? v + skip[i] : v;
-  a[i] = v;
-  if (a16) a16[i] = to_bf16(v);
-}
-
-// dz = da where mask > 0 (relu; the mask is z, or a = relu(z)) or da;
-// written to dz and (the GEMM operand) as bfloat16 into dz16 (either may be
-// null); the bias gradient's partial sums: block (x, o)
-// covers ACT_CHUNK entries of channel o's row (dz is [cout][P]) and writes
-// their sum, in a fixed order, to bpart[o][x]; and with a skip input (a =
-// act(z) + skip), its gradient: skip_da (+)= da.
+// dz16 = da where a = relu(z) > 0 (or da without relu), in bfloat16 (the GEMM
+// operand), and the bias gradient's partial sums: block (x, o) covers ACT_CHUNK
+// entries of channel o's row (dz is [cout][P]) and writes their sum, in a fixed
+// order, to bpart[o][x].
 constexpr int ACT_PER = 4;                 // entries per thread
 constexpr int ACT_CHUNK = EW * ACT_PER;   // entries per block
-__global__ __launch_bounds__(EW) void k_act_bwd(const float* __restrict__ da, const float* __restrict__ mask,
-                                                float* __restrict__ dz, bf16_t* __restrict__ dz16, int64_t P,
-                                                int relu, float* __restrict__ bpart, float* __restrict__ skip_da,
-                                                int skip_acc) {
+__global__ __launch_bounds__(EW) void k_act_bwd(const float* __restrict__ da, const float* __restrict__ a,
+                                                bf16_t* __restrict__ dz16, int64_t P, int relu,
+                                                float* __restrict__ bpart) {
   __shared__ float sh[EW / 64];
   const int o = blockIdx.y;
   const int64_t row = (int64_t)o * P;
@@ -377,19 +406,14 @@ __global__ __launch_bounds__(EW) void k_act_bwd(const float* __restrict__ da, co
     const int64_t p = p0 + (int64_t)r * EW;
     if (p < P) {
       const int64_t i = row + p;
-      const float d = da[i];
-      if (skip_da) skip_da[i] = skip_acc ? skip_da[i] + d : d;
-      const float v = (!relu || mask[i] > 0.0f) ? d : 0.0f;
-      if (dz) dz[i] = v;
-      if (dz16) dz16[i] = to_bf16(v);
+      const float v = (!relu || a[i] > 0.0f) ? da[i] : 0.0f;
+      dz16[i] = to_bf16(v);
       sum += v;
     }
   }
   sum = block_sum(sum, sh);
   if (threadIdx.x == 0) bpart[(int64_t)o * gridDim.x + blockIdx.x] = sum;
 }
-
-
 
 // db[o] = sum_p dz[o][p] of every layer from k_act_bwd's partial sums:
 // block b is channel b - first[l] of layer l, adding the layer's nchunk
@@ -453,35 +477,58 @@ __global__ __launch_bounds__(64 * SW) void k_sum_splits(const float* __restrict_
 // the input gradient is dsrc[c][s] = sum_{t, o} W[o][c][t] D[t][o][s] and the
 // weight gradient dW[o][c][t] = sum_s D[t][o][s] src[c][s] (s = (b, sy, sx)):
 // two GEMMs over the source grid, with no im2col or col2im pass and 1/4 of
-// the products of the upsampled grid.  One thread per (o, b, sy, sx) sums
-// the 4 x 4 outputs around it into all nine taps; D is bfloat16,
-// [9 cout][P4], P4 = batch Hs Ws.
-__global__ __launch_bounds__(EW) void k_dmap(const float* __restrict__ dz, int cout, int Bt, int Hs,
-                                             int Ws, bf16_t* __restrict__ D) {
-  const int pix = (int)(blockIdx.x * EW + threadIdx.x);
-  if (pix >= Hs * Ws) return;
-  const int o = blockIdx.y, b = blockIdx.z;
-  const int sy = pix / Ws, sx = pix - sy * Ws;
+// the products of the upsampled grid.  dz = da where mask is nonzero (relu) is formed
+// on the way: bound by memory, this reads da and the byte mask once and writes
+// only D (a pass that wrote dz and copied the skip gradient moved 16 to 20
+// bytes more an output).  One thread per (o, b, sy, sx) sums the 4 x 4 outputs
+// around it into all nine taps, taking the columns of its neighbours from their lanes; D is
+// bfloat16, [9 cout][P4], P4 = batch Hs Ws.  bpart: as in k_act_bwd, block (x,
+// o) summing the 2 x 2 outputs of its 256 source pixels.
+__global__ __launch_bounds__(EW) void k_dmap(const float* __restrict__ da, const uint8_t* __restrict__ mask,
+                                             int Bt, int Hs, int Ws, bf16_t* __restrict__ D,
+                                             float* __restrict__ bpart) {
+  __shared__ float sh[EW / 64];
+  const int P4 = Bt * Hs * Ws, s = (int)(blockIdx.x * EW + threadIdx.x);
+  const int o = blockIdx.y, cout = (int)gridDim.y, lane = threadIdx.x & 63;
+  const bool in = s < P4;
+  const int row = s / Ws, sx = s - row * Ws, b = row / Hs, sy = row - b * Hs;
   const int Ho = 2 * Hs, Wo = 2 * Ws;
-  const float* base = dz + ((int64_t)o * Bt + b) * Ho * Wo;
+  const int64_t base = ((int64_t)o * Bt + b) * Ho * Wo;
+  auto dz = [&](int64_t i) { return mask[i] ? da[i] : 0.0f; };
   float v[4][4];  // rows 2sy - 1 .. 2sy + 2, columns 2sx - 1 .. 2sx + 2
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int Y = 2 * sy - 1 + i, X = 2 * sx - 1 + j;
-      v[i][j] = (Y >= 0 && Y < Ho && X >= 0 && X < Wo) ? base[Y * Wo + X] : 0.0f;
+  for (int i = 0; i < 4; ++i) {
+    const int Y = 2 * sy - 1 + i;
+    const bool ok = in && Y >= 0 && Y < Ho;
+    const int64_t at = base + (int64_t)Y * Wo + 2 * sx;
+    float2 c = make_float2(0.0f, 0.0f);
+    if (ok) {
+      const float2 d = *(const float2*)(da + at);
+      const uint32_t m = *(const uint16_t*)(mask + at);
+      c = make_float2(m & 0xFFu ? d.x : 0.0f, m >> 8 ? d.y : 0.0f);
     }
-  const int64_t P4 = (int64_t)Bt * Hs * Ws;
-  const int64_t s = (int64_t)b * Hs * Ws + pix;
+    float l = __shfl_up(c.y, 1, 64), r = __shfl_down(c.x, 1, 64);
+    if (sx == 0) l = 0.0f;
+    else if (lane == 0) l = ok ? dz(at - 1) : 0.0f;
+    if (sx == Ws - 1) r = 0.0f;
+    else if (lane == 63) r = ok ? dz(at + 2) : 0.0f;
+    v[i][0] = l;
+    v[i][1] = c.x;
+    v[i][2] = c.y;
+    v[i][3] = r;
+  }
+  if (in) {
 #pragma unroll
-  for (int ky = 0; ky < 3; ++ky)
+    for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
-    for (int kx = 0; kx < 3; ++kx) {
-      // tap ky takes rows i = 2 - ky, 3 - ky of the 4 x 4 block
-      const float d = (v[2 - ky][2 - kx] + v[2 - ky][3 - kx]) + (v[3 - ky][2 - kx] + v[3 - ky][3 - kx]);
-      D[((int64_t)(3 * ky + kx) * cout + o) * P4 + s] = to_bf16(d);
-    }
+      for (int kx = 0; kx < 3; ++kx) {
+        // tap ky takes rows i = 2 - ky, 3 - ky of the 4 x 4 block
+        const float d = (v[2 - ky][2 - kx] + v[2 - ky][3 - kx]) + (v[3 - ky][2 - kx] + v[3 - ky][3 - kx]);
+        D[((int64_t)(3 * ky + kx) * cout + o) * P4 + s] = to_bf16(d);
+      }
+  }
+  const float sum = block_sum((v[1][1] + v[1][2]) + (v[2][1] + v[2][2]), sh);
+  if (threadIdx.x == 0) bpart[(int64_t)o * gridDim.x + blockIdx.x] = sum;
 }
 
 // Input gradient of a 3 x 3, stride-2, padding-1 convolution (input 2Ho x
@@ -688,7 +735,8 @@ struct lbm_no {
   float *par = nullptr, *grad = nullptr, *m = nullptr, *v = nullptr;
   bf16_t *wf = nullptr, *wt = nullptr, *wu = nullptr, *wph = nullptr;  // bfloat16 GEMM copies of the weights (Layer)
   int64_t wf_n = 0, wt_n = 0, wu_n = 0, wph_n = 0, wmax = 0;  // their sizes; k_prep's largest index space
-  std::vector<float*> z, a, da;  // per layer, [cout][B][Ho][Wo]
+  std::vector<float*> a, da;     // per layer, [cout][B][Ho][Wo]
+  std::vector<uint8_t*> zmask;   // upsampling layers: z > 0, [cout][B][Ho][Wo]
   std::vector<bf16_t*> colL;  // per layer: the forward's im2col, kept for the weight gradient
   bf16_t* col = nullptr;       // work: the backward's box sums (k_dmap) and shifted stacks (k_emap)
   bf16_t* dz16 = nullptr;  // bfloat16 copy of the current layer's dz
@@ -871,7 +919,7 @@ int im2col(lbm_no* h, const Layer& l, const float* src, bool nchw, int Bt, bf16_
 // phase GEMMs: phase (a, b) reads the taps dy in {a - 1, a}, dx in {b - 1,
 // b}, i.e. rows (3a + b) cin + [0, 2 cin) and, 3 cin further on, another
 // 2 cin rows.
-int forward_up(lbm_no* h, const Layer& l, const float* src, int Bt, bf16_t* col, float* z) {
+int forward_up(lbm_no* h, const Layer& l, const float* src, int Bt, bf16_t* col, float* a, const SkipT& sk) {
   const int64_t P4 = (int64_t)Bt * l.Hs * l.Ws;
   const dim3 grid(grid1((P4 + 1) / 2), (unsigned)l.cin);
   k_im2col<false, true><<<grid, EW, 0, h->stream>>>(src, l.cin, Bt, l.Hs, l.Ws, 0, 3, 1, 1, l.Hs, l.Ws, col);
@@ -886,7 +934,8 @@ int forward_up(lbm_no* h, const Layer& l, const float* src, int Bt, bf16_t* col,
   }
   ph.Hn = l.Hs;
   ph.Wn = l.Ws;
-  return gemm_phases(h, l.cout, (int)P4, h->wph + l.wph, l.Kph, col, P4, z, (int64_t)Bt * l.Ho * l.Wo, ph,
+  ph.sk = sk;
+  return gemm_phases(h, l.cout, (int)P4, h->wph + l.wph, l.Kph, col, P4, a, (int64_t)Bt * l.Ho * l.Wo, ph,
                      h->par + l.boff, 0);
 }
 
@@ -918,38 +967,34 @@ int input_grad_s2(lbm_no* h, const Layer& l, const bf16_t* dz, int Bt, float* dx
 // A 1 x 1, stride-1 layer: its im2col is its input in bfloat16.
 bool pointwise(const Layer& l) { return l.k == 1 && l.s == 1 && !l.up; }
 
-int forward_internal(lbm_no* h, const float* x, int Bt) {
+// grad: a backward follows (the relu masks of the layers with a skip input are kept).
+int forward_internal(lbm_no* h, const float* x, int Bt, bool grad) {
   bool col_ready = false;  // the layer's im2col was written with the previous layer's activation
   for (size_t li = 0; li < h->L.size(); ++li) {
     const Layer& l = h->L[li];
     const int64_t P = (int64_t)Bt * l.Ho * l.Wo;
     const int K = l.cin * l.k * l.k;
-    // a layer with a skip input keeps z (the relu mask of its backward) and
-    // adds the skip in k_act; any other layer's GEMM writes a = relu(z) (or
-    // z) itself, and its backward takes the mask from a (a > 0 exactly where
-    // z > 0)
+    // Every layer's GEMM writes a = relu(z) (or z) itself, and the backward takes
+    // the mask from a (a > 0 exactly where z > 0); the upsampling layers add their skip
+    // input to it and keep the mask as bytes.
     int rc = LBM_NO_OK;
     if (phase_kind(l) == 1) {
-      if (l.skip < 0) return fail(LBM_NO_EINVAL, "upsampling layer without a skip input");
-      rc = forward_up(h, l, h->a[li - 1], Bt, h->colL[li], h->z[li]);
-    } else {
-      if (!col_ready) rc = im2col(h, l, li == 0 ? x : h->a[li - 1], li == 0, Bt, h->colL[li]);
+      if (l.skip < 0 || !l.relu) return fail(LBM_NO_EINVAL, "upsampling layer without a skip input");
+      const bool next_pw = li + 1 < h->L.size() && pointwise(h->L[li + 1]);
+      rc = forward_up(h, l, h->a[li - 1], Bt, h->colL[li], h->a[li],
+                      SkipT{h->a[l.skip], next_pw ? h->colL[li + 1] : nullptr, grad ? h->zmask[li] : nullptr});
       if (rc) return rc;
-      // z[o][p] = W[o][k] col[k][p]: A k-contiguous, B n-contiguous
-      float* out = l.skip >= 0 ? h->z[li] : h->a[li];
-      rc = gemm<false>(h, l.cout, (int)P, K, h->wf + l.wf, l.Kp, h->colL[li], P, out, P, 0, 1, K,
-                       h->par + l.boff, 0, l.skip >= 0 ? 0 : l.relu);
-    }
-    if (rc) return rc;
-    const bool next_pw = li + 1 < h->L.size() && pointwise(h->L[li + 1]);
-    col_ready = false;
-    if (l.skip >= 0) {
-      const int64_t n = (int64_t)l.cout * P;
-      k_act<<<grid1(n), EW, 0, h->stream>>>(h->z[li], h->a[l.skip], h->a[li], n, l.relu,
-                                            next_pw ? h->colL[li + 1] : nullptr);
-      NOCHK(hipGetLastError());
       col_ready = next_pw;
+      continue;
     }
+    if (l.skip >= 0) return fail(LBM_NO_EINVAL, "skip input of a layer that is not upsampling");
+    if (!col_ready) rc = im2col(h, l, li == 0 ? x : h->a[li - 1], li == 0, Bt, h->colL[li]);
+    if (rc) return rc;
+    // a[o][p] = W[o][k] col[k][p]: A k-contiguous, B n-contiguous
+    rc = gemm<false>(h, l.cout, (int)P, K, h->wf + l.wf, l.Kp, h->colL[li], P, h->a[li], P, 0, 1, K,
+                     h->par + l.boff, 0, l.relu);
+    if (rc) return rc;
+    col_ready = false;
   }
   return LBM_NO_OK;
 }
@@ -1062,11 +1107,13 @@ int lbm_no_create(const int32_t* widths, int32_t height, int32_t width, int32_t 
       const int64_t P = (int64_t)max_batch * l.Ho * l.Wo;
       const size_t n = (size_t)l.cout * P * 4;
       actmax = std::max(actmax, (int64_t)l.cout * P);
-      float* zl = (float*)nalloc(h, n);
+      uint8_t* zl = l.up ? (uint8_t*)nalloc(h, n / 4) : nullptr;
       float* al = (float*)nalloc(h, n);
-      float* dl = (float*)nalloc(h, n);
-      if (!zl || !al || !dl) return bail(fail(LBM_NO_ENOMEM, "activations"));
-      h->z.push_back(zl);
+      bool skipped = false;  // a skip input: its gradient starts in the other layer's buffer
+      for (const Layer& y : h->L) skipped = skipped || y.skip == (int)li;
+      float* dl = skipped ? nullptr : (float*)nalloc(h, n);
+      if ((l.up && !zl) || !al || (!skipped && !dl)) return bail(fail(LBM_NO_ENOMEM, "activations"));
+      h->zmask.push_back(zl);
       h->a.push_back(al);
       h->da.push_back(dl);
       const int64_t K = (int64_t)l.cin * l.k * l.k;
@@ -1127,7 +1174,7 @@ int lbm_no_forward(lbm_no* h, const float* x, int32_t batch, float* y) {
     int rc = check_batch(h, batch);
     if (rc) return rc;
     if (!x || !y) return fail(LBM_NO_EINVAL, "null tensor");
-    rc = forward_internal(h, x, batch);
+    rc = forward_internal(h, x, batch, false);
     if (rc) return rc;
     const int64_t HW = (int64_t)h->H * h->W;
     k_to_nchw<<<grid1(3 * batch * HW), EW, 0, h->stream>>>(h->a.back(), batch, HW, y);
@@ -1141,7 +1188,7 @@ int lbm_no_gradients(lbm_no* h, const float* x, const float* target, int32_t bat
     int rc = check_batch(h, batch);
     if (rc) return rc;
     if (!x || !target) return fail(LBM_NO_EINVAL, "null tensor");
-    rc = forward_internal(h, x, batch);
+    rc = forward_internal(h, x, batch, true);
     if (rc) return rc;
     const int nl = (int)h->L.size();
     const int64_t HW = (int64_t)h->H * h->W;
@@ -1151,24 +1198,27 @@ int lbm_no_gradients(lbm_no* h, const float* x, const float* target, int32_t bat
     NOCHK(hipGetLastError());
     k_loss_final<<<1, EW, 0, h->stream>>>(h->lpart, nb, nout, h->dloss);
     NOCHK(hipGetLastError());
+    std::vector<float*> da(h->da);  // each layer's activation gradient
     std::vector<char> have(nl, 0);  // activation gradient already written
     have[nl - 1] = 1;
     for (int li = nl - 1; li >= 0; --li) {
       const Layer& l = h->L[li];
       const int64_t P = (int64_t)batch * l.Ho * l.Wo;
       const int K = l.cin * l.k * l.k;
-      // dz over z (and the bias gradient's partial sums); the skip passes da on unchanged
       const unsigned nchunk = (unsigned)((P + ACT_CHUNK - 1) / ACT_CHUNK);
-      float* skip_da = l.skip >= 0 ? h->da[l.skip] : nullptr;
-      // the relu mask: z where the layer has a skip input, else a (= relu(z)); dz over z
-      const float* mask = l.skip >= 0 ? h->z[li] : h->a[li];
-      // FP32 dz for the box sums of an upsampling layer, else bfloat16 dz for the GEMMs
-      k_act_bwd<<<dim3(nchunk, (unsigned)l.cout), EW, 0, h->stream>>>(h->da[li], mask, l.up ? h->z[li] : nullptr,
-                                                                       l.up ? nullptr : h->dz16, P, l.relu,
-                                                                       h->bpart + l.bpoff, skip_da,
-                                                                       l.skip >= 0 ? have[l.skip] : 0);
-      NOCHK(hipGetLastError());
-      if (l.skip >= 0) have[l.skip] = 1;
+      if (l.skip >= 0) {
+        // the skip passes da on unchanged: from here on the buffer is the skip layer's
+        // gradient, which later layers add to (dz is formed from it before, in k_dmap)
+        if (have[l.skip] || !l.up) return fail(LBM_NO_EINVAL, "skip input with another gradient");
+        da[l.skip] = da[li];
+        have[l.skip] = 1;
+      }
+      // bfloat16 dz for the GEMMs and the bias gradient's partial sums
+      if (!l.up) {
+        k_act_bwd<<<dim3(nchunk, (unsigned)l.cout), EW, 0, h->stream>>>(da[li], h->a[li], h->dz16, P, l.relu,
+                                                                         h->bpart + l.bpoff);
+        NOCHK(hipGetLastError());
+      }
       int S;
       int64_t kchunk;
       if (l.up) {
@@ -1176,8 +1226,8 @@ int lbm_no_gradients(lbm_no* h, const float* x, const float* target, int32_t bat
         // over the source grid from the box sums D = k_dmap(dz) (in col)
         const int64_t P4 = (int64_t)batch * l.Hs * l.Ws;
         const int M9 = 9 * l.cout;
-        k_dmap<<<dim3(grid1((int64_t)l.Hs * l.Ws), (unsigned)l.cout, (unsigned)batch), EW, 0, h->stream>>>(
-            h->z[li], l.cout, batch, l.Hs, l.Ws, h->col);
+        k_dmap<<<dim3(grid1(P4), (unsigned)l.cout), EW, 0, h->stream>>>(da[li], h->zmask[li], batch, l.Hs, l.Ws,
+                                                                        h->col, h->bpart + l.bpoff);
         NOCHK(hipGetLastError());
         // dW[o][c][t] = sum_s D[t cout + o][s] src[c][s]: A = D, B k(=s)-contiguous, the
         // source in bfloat16 being the centre tap (rows 4 cin ..) of the forward's im2col
@@ -1191,7 +1241,7 @@ int lbm_no_gradients(lbm_no* h, const float* x, const float* target, int32_t bat
                                                                          l.cout, l.cin);
         NOCHK(hipGetLastError());
         // da[li - 1][c][s] (+)= sum_{t, o} W[o][c][t] D[t cout + o][s]: A = wu, B = D n(=s)-contiguous
-        rc = gemm<false>(h, l.cin, (int)P4, M9, h->wu + l.wu, l.Kup, h->col, P4, h->da[li - 1], P4, 0, 1, M9,
+        rc = gemm<false>(h, l.cin, (int)P4, M9, h->wu + l.wu, l.Kup, h->col, P4, da[li - 1], P4, 0, 1, M9,
                          nullptr, have[li - 1]);
         if (rc) return rc;
         have[li - 1] = 1;
@@ -1209,14 +1259,14 @@ int lbm_no_gradients(lbm_no* h, const float* x, const float* target, int32_t bat
       NOCHK(hipGetLastError());
       if (li == 0) break;  // no gradient with respect to the input
       if (l.k == 1 && l.s == 1) {  // 1 x 1: the input gradient is the GEMM itself
-        rc = gemm<false>(h, K, (int)P, l.cout, h->wt + l.wt, l.coutp, h->dz16, P, h->da[li - 1], P, 0, 1, l.cout,
+        rc = gemm<false>(h, K, (int)P, l.cout, h->wt + l.wt, l.coutp, h->dz16, P, da[li - 1], P, 0, 1, l.cout,
                          nullptr, have[li - 1]);
         if (rc) return rc;
         have[li - 1] = 1;
         continue;
       }
       if (phase_kind(l) == 2) {
-        rc = input_grad_s2(h, l, h->dz16, batch, h->da[li - 1], have[li - 1]);
+        rc = input_grad_s2(h, l, h->dz16, batch, da[li - 1], have[li - 1]);
         if (rc) return rc;
         have[li - 1] = 1;
         continue;
