@@ -838,9 +838,9 @@ bool build_step_tiles(lbm_axi* h) {
 // 1.7, annulus 100 x 200 7.2 and 2.6, 300^2 8.0 and 4.1, 512^2 11.1 and 6.8, 64
 // of 128^2 30.6 and 18.7, 1000^2 26.5 and 17.8, the first 256 grids of the sweep
 // 449 and 302; FP16 200^2 9.0 and 5.6, 512^2 11.9 and 9.3.  In 16-bit storage
-// single steps take over where the tiles come to more than one for each compute
-// unit (550^2: 13.1 and 14.4, four of 300^2 12.2 and 14.7): they move half the
-// bytes, and the halo's roundings cost more.
+// single steps take over where the tiles come to more than one round (FP16 600^2
+// 13.2 and 10.0, four of 300^2 12.2 and 11.0, but 2000^2 55 and 75 at best): they
+// move half the bytes, and the halo's roundings cost more.
 // The tile kernel's radial walls are those of the step kernels with wall lanes,
 // bit for bit.  Handles without them by default (rows of more than 2560 columns)
 // take tiles in FP32, where the two differ by rounding: 8192^2 runs 1414 us a step
@@ -861,11 +861,11 @@ void plan_tiles(lbm_axi* h) {
     bytes += (size_t)D.plane * (14 * esz + (esz == 2 ? 4 : 0));
     nodes += (double)D.nr * D.nz;
   }
-  if (esz == 2 && nodes > 3e5) return;
+  if (esz == 2 && nodes > 5e5) return;  // no round of tiles holds them
   // the second set of planes: at most a sixteenth of the device's memory
   size_t free_b = 0, total = 0;
   if (hipMemGetInfo(&free_b, &total) != hipSuccess || bytes > total / 16 || bytes > free_b / 4) return;
-  h->tile_m = nodes <= 1e5 ? 8 : (nodes <= 4e5 ? 6 : 4);
+  h->tile_m = nodes <= 1e5 ? 8 : (nodes <= (esz == 4 ? 4e5 : 3e5) ? 6 : 4);
   for (const InstDev& D : h->hdesc) h->tile_m = std::min(h->tile_m, tile_max_steps(D));
   auto tiles = [&](int rows) {
     int walls;
@@ -876,8 +876,12 @@ void plan_tiles(lbm_axi* h) {
   if (nodes <= 1e5) {
     for (int rows = 5; rows <= 28; ++rows)
       if (tiles(rows) <= TILE_CUS) break;
-  } else if (nodes <= 4e5) {
+  } else if (h->tile_m == 6) {
     h->tile_h = 28;
+  } else if (esz == 2) {
+    int rows = 26;
+    while (rows <= 34 && tiles(rows) > 2 * TILE_CUS) rows += 2;
+    if (rows > 34) return;
   } else {
     int best = 30;
     const int64_t round = 2 * TILE_CUS;
