@@ -10,9 +10,9 @@ before the timed region starts.
 
 Prints one JSON line: MLUPS (million node updates per second, one node = both
 lattices), the HBM roofline of the step kernel (algorithmic bytes per launch
-over its average duration from HIP events on the library's stream) and the
-FP64 CPU oracle timed on a bounded sample of the same problem (all host
-threads and one).  Also on the line: the same job with its host hand-overs
+over its average duration from HIP events on the library's stream, over up to
+200 further steps with one launch each) and the FP64 CPU oracle timed on a
+bounded sample of the same problem (all host threads and one).  Also on the line: the same job with its host hand-overs
 (create, field read-back), the FP16 and BF16 storage variants, the
 1024-instance batched sweep, and the time to steady state of 64 held-out
 128^2 problems from a cold start, from the learned warm start and from the
@@ -37,7 +37,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_kernel_traffic_8192.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1409_5929_amd", "csrc", f)
                   for f in ("lbm_axi.hip", "lbm_axi_s16.hip", "lbm_axi_kernels.h", "lbm_axi_dev.h",
-                            "lbm_axi_desc.h")]
+                            "lbm_axi_desc.h", "lbm_axi_tile.h")]
 
 
 def log(msg):
@@ -451,7 +451,6 @@ def main():
         del src, dst
 
     log(f"timed {args.steps} steps")
-    lat.set_timing(True)
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
@@ -460,10 +459,16 @@ def main():
     e1.record(stream)
     torch.cuda.synchronize()
     total_ms = e0.elapsed_time(e1)
-    kern_ms, launches = lat.kernel_time()
-    lat.set_timing(False)
     res = lat.residual()
     info = lat.info()
+    # the roofline of one step's kernel, from events around its launches: a handle
+    # that times its launches takes one step per launch, so this leg comes after
+    kt0, ksteps = int(info["t"]), min(args.steps, 200)
+    log(f"step kernel: {ksteps} steps, one launch each")
+    lat.set_timing(True)
+    lat.step(ksteps)
+    kern_ms, launches = lat.kernel_time()
+    lat.set_timing(False)
     log("pattern ceiling probe")
     pattern = pattern_ceiling(lat)
     t_read = time.perf_counter()
@@ -490,8 +495,7 @@ def main():
     # 14 populations read + 14 written, porosity read; g_0 stays FP32 in 16-bit storage
     bytes_node = 116 if args.storage == "fp32" else 26 * 2 + 2 * 4 + 4
     # launches that also write u_z, u_r, T for the check (one per check interval)
-    t0 = args.warmup
-    macro_launches = sum(1 for t in range(t0, t0 + args.steps)
+    macro_launches = sum(1 for t in range(kt0, kt0 + ksteps)
                          if args.check_interval > 0 and t % args.check_interval == 0)
     alg_bytes = launches * fluid * bytes_node + macro_launches * 12 * n * n
     avg_ms = kern_ms / max(launches, 1)
@@ -524,7 +528,8 @@ def main():
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
-            "kernel": "k_step (fused collide-stream, even and odd AA variants)",
+            "kernel": "k_step (fused collide-stream, even and odd AA variants), one step per launch, timed "
+                      "after the timed region (which takes several steps per launch on LDS tiles in FP32)",
             "bytes_per_node": bytes_node,
             "avg_launch_ms": round(avg_ms, 5),
             "launches": launches,

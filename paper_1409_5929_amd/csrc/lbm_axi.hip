@@ -591,10 +591,25 @@ int launch_step(lbm_axi* h, bool buf, bool odd, int mode, const StepLaunch& L, i
   return launch_result(e, "step kernel launch");
 }
 
-int launch_fields(lbm_axi* h, int inst, bool odd, const FieldOut& fo) {
+// Fields of one instance at its own level.  Reading the level back from the device
+// first cost 30 us a call (two copies and a wait, of 57 in all for 64^2); the
+// launch of both parities, of which one returns at once, costs a few.  A handle that
+// never checks has only running instances, and on grids of many blocks the idle
+// launch costs more than the copy.
+int launch_fields(lbm_axi* h, int inst, const FieldOut& fo) {
   const StepLaunch L = inst_launch(h, inst);
-  return launch_result(h->storage == LBM_STORE_FP32 ? launch_fields_t<float>(odd, L, fo)
-                                                    : launch_fields_s16(h->storage, odd, L, fo),
+  long long t = h->t;
+  const long long* t_stop = nullptr;
+  if (h->check > 0 && L.ntiles <= 8192) {
+    t_stop = &h->dres[inst].t_stop;
+  } else if (h->check > 0) {
+    int64_t info[4];
+    const int rc = lbm_axi_info(h, inst, info);
+    if (rc) return rc;
+    t = info[0];
+  }
+  return launch_result(h->storage == LBM_STORE_FP32 ? launch_fields_t<float>(t, t_stop, L, fo)
+                                                    : launch_fields_s16(h->storage, t, t_stop, L, fo),
                        "field kernel launch");
 }
 
@@ -1591,10 +1606,6 @@ namespace {
 int fields_to(lbm_axi* h, int inst, const FieldOut& out, int dst_is_device) {
   return guarded([&]() -> int {
     if (!h || inst < 0 || inst >= h->n_inst) return fail(LBM_AXI_EINVAL, "bad handle or instance");
-    int64_t info[4];
-    int rc = lbm_axi_info(h, inst, info);
-    if (rc) return rc;
-    const bool odd = (info[0] & 1) != 0;
     const lbm_axi_params& q = h->prm[inst];
     const size_t n = (size_t)q.nr * q.nz;
     FieldOut fo = out;
@@ -1623,7 +1634,7 @@ int fields_to(lbm_axi* h, int inst, const FieldOut& out, int dst_is_device) {
         fo.mask = (uint8_t*)d;
       }
     }
-    rc = launch_fields(h, inst, odd, fo);
+    int rc = launch_fields(h, inst, fo);
     if (!rc && !dst_is_device) {
       hipError_t e = hipSuccess;
       if (uz && e == hipSuccess) e = hipMemcpyAsync(uz, fo.uz, sizeof(float) * n, hipMemcpyDeviceToHost, h->stream);
@@ -1666,10 +1677,6 @@ int lbm_axi_stream_function(lbm_axi* h, int32_t inst, float* psi, double* psi_ab
                             int32_t dst_is_device) {
   return guarded([&]() -> int {
     if (!h || inst < 0 || inst >= h->n_inst) return fail(LBM_AXI_EINVAL, "bad handle or instance");
-    int64_t info[4];
-    int rc = lbm_axi_info(h, inst, info);
-    if (rc) return rc;
-    const bool odd = (info[0] & 1) != 0;
     const lbm_axi_params& q = h->prm[inst];
     const size_t n = (size_t)q.nr * q.nz;
     void *duz = nullptr, *dcol = nullptr, *dmax = nullptr, *dpsi = nullptr;
@@ -1690,7 +1697,7 @@ int lbm_axi_stream_function(lbm_axi* h, int32_t inst, float* psi, double* psi_ab
       return fail(LBM_AXI_ENOMEM, "stream function staging");
     }
     FieldOut fo{(float*)duz, nullptr, nullptr, nullptr, nullptr, nullptr};
-    rc = launch_fields(h, inst, odd, fo);
+    int rc = launch_fields(h, inst, fo);
     if (!rc) {
       k_psi<<<(q.nz + RB / 64 - 1) / (RB / 64), RB, 0, h->stream>>>(
           (const float*)duz, q.nr, q.nz, q.r0, q.side_rmin == LBM_SIDE_AXIS ? 1 : 0, (float*)dpsi,
@@ -1716,14 +1723,10 @@ int lbm_axi_stream_function_static(lbm_axi* h, int32_t inst, float* psi, double*
     if ((int64_t)q.nr * q.nz > SCRATCH_NODES || q.nz > SCRATCH_COLS)
       return fail(LBM_AXI_EINVAL, "instance larger than the static scratch (2^23 nodes, 2^16 columns)");
     if (!h->scratch) return fail(LBM_AXI_EDEVICE, "no scratch address for this device");
-    int64_t info[4];
-    int rc = lbm_axi_info(h, inst, info);  // run state and time level: a copy to the host, no allocation
-    if (rc) return rc;
-    const bool odd = (info[0] & 1) != 0;
     float* duz = (float*)h->scratch;
     double* dcol = (double*)((unsigned char*)h->scratch + SCRATCH_NODES * 4);
     FieldOut fo{duz, nullptr, nullptr, nullptr, nullptr, nullptr};
-    rc = launch_fields(h, inst, odd, fo);
+    int rc = launch_fields(h, inst, fo);
     if (rc) return rc;
     k_psi<<<(q.nz + RB / 64 - 1) / (RB / 64), RB, 0, h->stream>>>(
         duz, q.nr, q.nz, q.r0, q.side_rmin == LBM_SIDE_AXIS ? 1 : 0, psi, dcol);
@@ -1739,10 +1742,6 @@ int lbm_axi_pipe_nusselt(lbm_axi* h, int32_t inst, int32_t area, double* nu, dou
     const lbm_axi_params& q = h->prm[inst];
     if (q.side_rmin != LBM_SIDE_AXIS || q.side_rmax != LBM_SIDE_WALL)
       return fail(LBM_AXI_EINVAL, "pipe Nusselt numbers need an axis at r_min and a wall at r_max");
-    int64_t info[4];
-    int rc = lbm_axi_info(h, inst, info);
-    if (rc) return rc;
-    const bool odd = (info[0] & 1) != 0;
     const size_t n = (size_t)q.nr * q.nz;
     void *dT = nullptr, *dU = nullptr, *dnu = nullptr, *dtb = nullptr;
     auto release_tmp = [&]() {
@@ -1756,7 +1755,7 @@ int lbm_axi_pipe_nusselt(lbm_axi* h, int32_t inst, int32_t area, double* nu, dou
       return fail(LBM_AXI_ENOMEM, "pipe Nusselt staging");
     }
     FieldOut fo{(float*)dU, nullptr, nullptr, (float*)dT, nullptr, nullptr};
-    rc = launch_fields(h, inst, odd, fo);
+    int rc = launch_fields(h, inst, fo);
     if (!rc) {
       k_pipe_nu<<<(q.nz + RB / 64 - 1) / (RB / 64), RB, 0, h->stream>>>(
           (const float*)dT, (const float*)dU, area ? 1 : 0, q.nr, q.nz, q.r0, (double*)dnu, (double*)dtb);

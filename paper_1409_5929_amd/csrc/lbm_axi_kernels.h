@@ -27,9 +27,14 @@ __global__ __launch_bounds__(BX* BY) __attribute__((amdgpu_waves_per_eu(sizeof(S
                                                  const long long* __restrict__ clk, int off) {
   // Inside a captured step graph the time level comes from the device clock
   // (set before every replay) plus the step's offset in the graph.
-  if (clk) seed = step_seed(*clk + off);
+  if (MODE != MODE_FIELDS && clk) seed = step_seed(*clk + off);
   const int4 tl = tiles[blockIdx.x];
   if (tl.x < 0) return;
+  if constexpr (MODE == MODE_FIELDS) {
+    // the kernel of the instance's parity works: off while it runs, else that of
+    // the level at which it stopped
+    if (clk && (((status[tl.x] == RUN ? off : *clk) & 1) != 0) != ODD) return;
+  }
   if (MODE != MODE_FIELDS && status[tl.x] != RUN) return;
   const InstDev D = descs[tl.x];
   // A packed tile (tl.w = 1) covers 32 columns: lanes 32..63 take the z strip
@@ -194,14 +199,18 @@ hipError_t launch_step_b(bool wall_lanes, bool odd, int mode, const StepLaunch& 
   return wall_lanes ? launch_step_t<S, BUF, true>(odd, mode, L, mac_slot, seed, clk, off)
                     : launch_step_t<S, BUF, false>(odd, mode, L, mac_slot, seed, clk, off);
 }
-// Macroscopic fields of one instance (no population writes).
+// Macroscopic fields of one instance (no population writes).  The state's layout
+// follows the parity of the instance's level: the handle's level t, or t_stop (device
+// memory) once it has stopped.  With t_stop both parities are launched and the device
+// picks; without, the handle's level counts.
 template <typename S>
-hipError_t launch_fields_t(bool odd, const StepLaunch& L, const FieldOut& fo) {
+hipError_t launch_fields_t(long long t, const long long* t_stop, const StepLaunch& L, const FieldOut& fo) {
   const dim3 blk(BX, BY);
-  if (!odd)
-    k_step<S, false, MODE_FIELDS, false><<<L.ntiles, blk, 0, L.stream>>>(L.descs, L.tiles, L.status, L.kz, 0, fo, 0u, nullptr, 0);
-  else
-    k_step<S, true, MODE_FIELDS, false><<<L.ntiles, blk, 0, L.stream>>>(L.descs, L.tiles, L.status, L.kz, 0, fo, 0u, nullptr, 0);
+  const int odd = (int)(t & 1);
+  if (t_stop || !odd)
+    k_step<S, false, MODE_FIELDS, false><<<L.ntiles, blk, 0, L.stream>>>(L.descs, L.tiles, L.status, L.kz, 0, fo, 0u, t_stop, odd);
+  if (t_stop || odd)
+    k_step<S, true, MODE_FIELDS, false><<<L.ntiles, blk, 0, L.stream>>>(L.descs, L.tiles, L.status, L.kz, 0, fo, 0u, t_stop, odd);
   return hipGetLastError();
 }
 // Streaming-ceiling probe with the step's launch and addressing.
@@ -243,7 +252,7 @@ hipError_t launch_tile_t(const TileLaunch& L, int nsteps, long long t) {
 // LBM_STORE_BF16.  Each returns the launch's hipError_t.
 hipError_t launch_step_s16(int storage, bool buf, bool wall_lanes, bool odd, int mode, const StepLaunch& L,
                            int mac_slot, uint32_t seed, const long long* clk, int off);
-hipError_t launch_fields_s16(int storage, bool odd, const StepLaunch& L, const FieldOut& fo);
+hipError_t launch_fields_s16(int storage, long long t, const long long* t_stop, const StepLaunch& L, const FieldOut& fo);
 hipError_t launch_pattern_s16(int storage, bool buf, bool odd, const StepLaunch& L, uint32_t key);
 hipError_t launch_tile_s16(int storage, const TileLaunch& L, int nsteps, long long t);
 hipError_t launch_init_s16(int storage, const StepLaunch& L, const float* dinit, float T_init, int inst);

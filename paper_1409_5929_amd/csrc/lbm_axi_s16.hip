@@ -28,9 +28,9 @@ hipError_t launch_step_s16(int storage, bool buf, bool wall_lanes, bool odd, int
   return step_s<__hip_bfloat16>(buf, wall_lanes, odd, mode, L, mac_slot, seed, clk, off);
 }
 
-hipError_t launch_fields_s16(int storage, bool odd, const StepLaunch& L, const FieldOut& fo) {
-  if (storage == LBM_STORE_FP16) return launch_fields_t<__half>(odd, L, fo);
-  return launch_fields_t<__hip_bfloat16>(odd, L, fo);
+hipError_t launch_fields_s16(int storage, long long t, const long long* t_stop, const StepLaunch& L, const FieldOut& fo) {
+  if (storage == LBM_STORE_FP16) return launch_fields_t<__half>(t, t_stop, L, fo);
+  return launch_fields_t<__hip_bfloat16>(t, t_stop, L, fo);
 }
 
 hipError_t launch_pattern_s16(int storage, bool buf, bool odd, const StepLaunch& L, uint32_t key) {

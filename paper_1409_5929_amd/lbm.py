@@ -295,17 +295,22 @@ class Lattice:
         stream.  The tensors belong to torch's current stream: unless the
         handle runs on that very stream, this waits for the handle's stream
         before returning, so that neither a reader nor torch's allocator sees
-        them before they are written."""
+        them before they are written.  It waits for torch's stream first: the
+        memory of new tensors may still be in use there."""
         import torch
 
         nz, nr = self.shapes[inst]
+        cur = torch.cuda.current_stream()
+        # A zero stream value means the library created its own stream.
+        other = self._stream == 0 or self._stream != (cur.cuda_stream or 0)
         out = {k: torch.empty((nz, nr), dtype=torch.float32, device="cuda")
                for k in ("uz", "ur", "p", "T")}
+        if other:
+            cur.synchronize()
         _check(self._lib.lbm_axi_macros(self._h, int(inst), out["uz"].data_ptr(),
                                         out["ur"].data_ptr(), out["p"].data_ptr(),
                                         out["T"].data_ptr(), None, 1))
-        # A zero stream value means the library created its own stream.
-        if self._stream == 0 or self._stream != (torch.cuda.current_stream().cuda_stream or 0):
+        if other:
             self.sync()
         return out
 
