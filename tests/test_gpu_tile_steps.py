@@ -105,3 +105,23 @@ def test_wide_grids_take_tiles_within_rounding(L, nr, nz):  # noqa: F811
     for k in ("uz", "ur", "T"):
         a, b = got[0][k].astype(np.float64), got[1][k].astype(np.float64)
         assert np.linalg.norm(a - b) <= 2e-6 * np.linalg.norm(b), k
+
+
+@pytest.mark.parametrize("storage", ["fp32", "fp16"])
+def test_fields_of_a_stopped_instance_are_those_of_its_own_level(L, storage):  # noqa: F811
+    """An instance that stops at the check of step 20 stays at level 21 while the
+    other one goes on to an even level: each is read at its own parity."""
+    quiet = dict(li.annulus(nr=40, nz=24, Ra=1e4, Da=1e-3), tol=10.0)
+    other = li.annulus(nr=33, nz=50, Ra=1e5, Da=1e-3)
+    lat = L.Lattice([quiet, other], storage=storage, check_interval=20)
+    lat.step(40)
+    assert lat.info(0)["status"] == "converged" and lat.info(0)["t"] == 21 and lat.info(1)["t"] == 40
+    for i, (cfg, n) in enumerate(((quiet, 21), (other, 40))):
+        one = L.Lattice([cfg], storage=storage, check_interval=0)
+        one.step(n)
+        same(lat.fields(i), one.fields(0), f"instance {i}")
+        d = lat.fields_device(i)
+        for k in ("uz", "ur", "p", "T"):
+            np.testing.assert_array_equal(d[k].cpu().numpy(), one.fields(0)[k])
+        one.close()
+    lat.close()
