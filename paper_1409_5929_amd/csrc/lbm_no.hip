@@ -628,8 +628,9 @@ struct Layer {
   int Ho, Wo;    // output size
   int64_t woff, boff;
   // bfloat16 GEMM copies of the weights, rows padded to multiples of 8
-  // elements (16 bytes): wf[cout][Kp] (forward) and wt[K][coutp] (input
-  // gradient), at these element offsets of lbm_no::wf / lbm_no::wt
+  // elements (16 bytes): wf[cout][Kp] (forward, not of upsampling layers) and
+  // wt[K][coutp] (input gradient of 1 x 1 layers), at these element offsets of
+  // lbm_no::wf / lbm_no::wt (-1: none)
   int Kp, coutp;
   int64_t wf, wt;
   // upsampling layers: wu[c][Kup] with wu[c][t cout + o] = W[o][c][t] (the
@@ -708,8 +709,8 @@ __global__ __launch_bounds__(EW) void k_prep(const float* __restrict__ par, Prep
   }
   const int o = (int)(i / K), k = (int)(i - (int64_t)o * K);
   const bf16_t v = to_bf16(par[t.woff[l] + i]);
-  wf[t.wf[l] + (int64_t)o * t.Kp[l] + k] = v;
-  wt[t.wt[l] + (int64_t)k * t.coutp[l] + o] = v;
+  if (t.wf[l] >= 0) wf[t.wf[l] + (int64_t)o * t.Kp[l] + k] = v;
+  if (t.wt[l] >= 0) wt[t.wt[l] + (int64_t)k * t.coutp[l] + o] = v;
   if (t.wu[l] >= 0) {  // k = c taps + tap
     const int c = k / t.taps[l], tap = k - c * t.taps[l];
     wu[t.wu[l] + (int64_t)c * t.Kup[l] + tap * t.cout[l] + o] = v;
@@ -1073,10 +1074,10 @@ int lbm_no_create(const int32_t* widths, int32_t height, int32_t width, int32_t 
       const int K = l.cin * l.k * l.k;
       l.Kp = (K + 7) / 8 * 8;
       l.coutp = (l.cout + 7) / 8 * 8;
-      l.wf = h->wf_n;
-      l.wt = h->wt_n;
-      h->wf_n += (int64_t)l.cout * l.Kp;
-      h->wt_n += (int64_t)K * l.coutp;
+      l.wf = phase_kind(l) == 1 ? -1 : h->wf_n;
+      l.wt = pointwise(l) ? h->wt_n : -1;
+      if (l.wf >= 0) h->wf_n += (int64_t)l.cout * l.Kp;
+      if (l.wt >= 0) h->wt_n += (int64_t)K * l.coutp;
       int64_t nprep = (int64_t)l.cout * K;
       if (l.up) {
         l.Kup = (l.k * l.k * l.cout + 7) / 8 * 8;
