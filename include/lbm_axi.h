@@ -398,6 +398,13 @@ int lbm_axi_set_storage(lbm_axi* h, int32_t storage, int32_t storage_shift);
 int lbm_axi_set_graph(lbm_axi* h, int32_t steps);
 
 /*
+ * How the handle's steps so far were launched (host counters; no wait): out[0] =
+ * steps launched one by one, out[1] = steps in replays of the captured graph,
+ * out[2] = steps taken several to a launch.  out has 3 entries.
+ */
+int lbm_axi_step_paths(lbm_axi* h, int64_t* out);
+
+/*
  * Drops instances that are no longer running (converged, diverged, stalled)
  * from the step launch, so that a batch whose instances finish at different
  * times stops paying for the finished ones.  Reads the run states (waits for

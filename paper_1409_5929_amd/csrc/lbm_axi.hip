@@ -130,6 +130,7 @@ struct lbm_axi {
   DevResult* dres = nullptr;
   int* dfirst = nullptr;        // per-instance first reduction tile and count
   long long t = 0;              // global time level
+  int64_t steps_by[3] = {0, 0, 0};  // steps taken in single launches, graph replays, on tiles
   size_t bytes = 0;
   bool timing = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev;
@@ -972,6 +973,7 @@ int tile_steps(lbm_axi* h, int n) {
     if (rc) return rc;
     done += s;
   }
+  h->steps_by[2] += n;
   h->t += n;
   return LBM_AXI_OK;
 }
@@ -1340,6 +1342,7 @@ int lbm_axi_step(lbm_axi* h, int32_t nsteps) {
         k_setclock<<<1, 1, 0, h->stream>>>(h->dclk, n);
         HIPCHK(hipGetLastError());
         HIPCHK(hipGraphLaunch(h->gexec, h->stream));
+        h->steps_by[1] += G;
         h->t = n + G;
         continue;
       }
@@ -1380,10 +1383,17 @@ int lbm_axi_step(lbm_axi* h, int32_t nsteps) {
                                                   h->dtail, h->dmx, h->dnus, h->dstatus, h->dres);
         HIPCHK(hipGetLastError());
       }
+      ++h->steps_by[0];
       h->t = n + 1;
     }
     return LBM_AXI_OK;
   });
+}
+
+int lbm_axi_step_paths(lbm_axi* h, int64_t* out) {
+  if (!h || !out) return fail(LBM_AXI_EINVAL, "bad handle or output");
+  for (int i = 0; i < 3; ++i) out[i] = h->steps_by[i];
+  return LBM_AXI_OK;
 }
 
 int lbm_axi_set_graph(lbm_axi* h, int32_t steps) {

@@ -154,6 +154,8 @@ def _load():
     lib.lbm_axi_set_storage.restype = ctypes.c_int
     lib.lbm_axi_set_graph.argtypes = [ctypes.c_void_p, ctypes.c_int32]
     lib.lbm_axi_set_graph.restype = ctypes.c_int
+    lib.lbm_axi_step_paths.argtypes = [ctypes.c_void_p, P(ctypes.c_int64)]
+    lib.lbm_axi_step_paths.restype = ctypes.c_int
     lib.lbm_axi_compact.argtypes = [ctypes.c_void_p, P(ctypes.c_int32)]
     lib.lbm_axi_compact.restype = ctypes.c_int
     lib.lbm_axi_autotune.argtypes = [ctypes.c_void_p, ctypes.c_int32, P(ctypes.c_int32),
@@ -397,6 +399,13 @@ class Lattice:
     def set_graph(self, steps: int):
         """Steps per captured step graph (even, 0 disables)."""
         _check(self._lib.lbm_axi_set_graph(self._h, int(steps)))
+
+    def step_paths(self) -> dict:
+        """Steps so far by how they were launched: one by one, in replays of the
+        captured graph, several to a launch on LDS tiles."""
+        out = (ctypes.c_int64 * 3)()
+        _check(self._lib.lbm_axi_step_paths(self._h, out))
+        return dict(zip(("single", "graph", "tiles"), list(out)))
 
     def compact(self) -> int:
         """Drop finished instances from the step launch; returns the number running."""
