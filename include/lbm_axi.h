@@ -391,9 +391,8 @@ int lbm_axi_set_storage(lbm_axi* h, int32_t storage, int32_t storage_shift);
  * rest are launched one by one.  Results are identical either way.  steps is
  * even, 0..4096; 0 disables graphs; default 32.  Launch timing
  * (lbm_axi_set_timing) bypasses the graphs.  Where the library takes several
- * plain steps per launch instead (handles with wall lanes in FP32 storage, and
- * in 16-bit storage up to about 400000 nodes; again with identical results),
- * graphs are not used.  Waits for the stream.
+ * plain steps per launch instead (FP32 storage, and 16-bit storage up to about
+ * 400000 nodes; again with identical results, bit for bit), graphs are not used.  Waits for the stream.
  */
 int lbm_axi_set_graph(lbm_axi* h, int32_t steps);
 

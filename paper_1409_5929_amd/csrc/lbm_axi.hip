@@ -139,13 +139,12 @@ struct lbm_axi {
   std::vector<char> active;     // instances in the launch list (empty: all)
   bool buf = false;             // step kernels use buffer addressing (all arrays below 4 GiB)
   bool wall_lanes = false;      // step kernels compute radial wall nodes on their own lanes
-  int wall_mode = -1;           // as lbm_axi_set_wall_lanes set it
   long long* dclk = nullptr;    // device clock of captured step graphs
   int graph_steps = 32;         // steps per captured graph (0: no graphs)
   // steps on LDS tiles (k_tile): 0 not planned yet, 1 planned, -1 not used
   int tile_plan = 0;
   int tile_m = 0, tile_h = 0;               // most steps per launch, rows per tile
-  int tile_nf = 0, tile_nt = 0, tile_lds = 0;  // fluid threads, threads, LDS bytes of a block
+  int tile_lds = 0;                         // LDS bytes of a block
   StepTile* dsteptiles = nullptr;  // own allocation
   int nsteptiles = 0;
   InstDev* ddesc_b = nullptr;      // descriptors of the second set of planes
@@ -808,7 +807,7 @@ std::vector<StepTile> step_tiles(const lbm_axi* h, bool live, int& walls, size_t
         const TileRegion g = tile_load_region(D, out.back(), h->tile_m);
         const size_t n = (size_t)(g.kh - g.kl) * TILE_VW;
         lds = std::max(lds, h->storage == LBM_STORE_FP32 ? tile_bytes<float>(n) : tile_bytes<__half>(n));
-        walls = std::max(walls, tile_walls<true>(D, g).count);
+        walls = std::max(walls, tile_wall_threads(h->wall_lanes ? tile_walls<true>(D, g) : tile_walls<false>(D, g)));
       }
   }
   return out;
@@ -819,10 +818,8 @@ bool build_step_tiles(lbm_axi* h) {
   int walls = 0;
   size_t lds = 0;
   const std::vector<StepTile> live = step_tiles(h, true, walls, lds);
-  h->tile_nt = TILE_NT;
-  h->tile_nf = TILE_NT - (walls + 63) / 64 * 64;
   h->tile_lds = (int)lds;
-  if (h->tile_nf < TILE_NT / 2 || lds > (size_t)h->lds_per_block) return false;
+  if (walls > TILE_NT / 2 || lds > (size_t)h->lds_per_block) return false;
   for (const StepTile& T : live)
     if (!tile_inside(h->hdesc[T.inst], T, h->tile_m)) return false;
   const int T = (int)live.size(), per = T > 0 ? (T + 7) / 8 : 1;
@@ -857,15 +854,12 @@ bool build_step_tiles(lbm_axi* h) {
 // single steps take over where the tiles come to more than one round (FP16 600^2
 // 13.2 and 10.0, four of 300^2 12.2 and 11.0, but 2000^2 55 and 75 at best): they
 // move half the bytes, and the halo's roundings cost more.
-// The tile kernel's radial walls are those of the step kernels with wall lanes,
-// bit for bit.  Handles without them by default (rows of more than 2560 columns)
-// take tiles in FP32, where the two differ by rounding: 8192^2 runs 1414 us a step
-// in single steps and 1026 on tiles.  In 16-bit storage, whose stochastic rounding would
-// turn that into other bits, and where the caller has switched wall lanes
-// off, they do not.
+// Every node comes out as in the handle's single steps, bit for bit: the node code
+// and its fused products are the same, and so is who computes the radial walls (the
+// handle's wall-lane setting).  A wide grid without wall lanes gains as much: 8192^2
+// FP32 runs 1414 us a step in single steps and 917 on tiles.
 void plan_tiles(lbm_axi* h) {
   h->tile_plan = -1;
-  if (!h->wall_lanes && (h->wall_mode == 0 || h->storage != LBM_STORE_FP32)) return;
   const size_t esz = h->storage == LBM_STORE_FP32 ? 4 : 2;
   size_t bytes = 0;
   double nodes = 0.0;
@@ -966,9 +960,10 @@ int tile_steps(lbm_axi* h, int n) {
   for (int i = 0; i < L; ++i) {
     const int s = 2 * (int)((int64_t)(n / 2) * (i + 1) / L) - done;
     const TileLaunch t{i & 1 ? h->ddesc_b : h->ddesc, i & 1 ? h->ddesc : h->ddesc_b, h->dsteptiles, h->dstatus,
-                       h->nsteptiles, h->tile_nf, h->tile_nt, h->tile_lds, h->stream};
-    const hipError_t e = h->storage == LBM_STORE_FP32 ? launch_tile_t<float>(t, s, h->t + done)
-                                                      : launch_tile_s16(h->storage, t, s, h->t + done);
+                       h->nsteptiles, h->tile_lds, h->stream};
+    const hipError_t e = h->storage == LBM_STORE_FP32
+                             ? launch_tile_t<float>(h->wall_lanes, t, s, h->t + done)
+                             : launch_tile_s16(h->storage, h->wall_lanes, t, s, h->t + done);
     const int rc = launch_result(e, "tile kernel launch");
     if (rc) return rc;
     done += s;
@@ -1566,8 +1561,7 @@ int lbm_axi_set_wall_lanes(lbm_axi* h, int32_t mode, int32_t* on) {
     HIPCHK(hipStreamSynchronize(h->stream));
     const bool want = mode < 0 ? default_wall_lanes(h) : mode == 1;
     if (want != h->wall_lanes) drop_graph(h);  // captured graphs hold the other kernels
-    if (want != h->wall_lanes || mode != h->wall_mode) drop_tile_plan(h);
-    h->wall_mode = mode;
+    if (want != h->wall_lanes) drop_tile_plan(h);  // as tiles do
     h->wall_lanes = want;
     if (on) *on = want ? 1 : 0;
     return LBM_AXI_OK;

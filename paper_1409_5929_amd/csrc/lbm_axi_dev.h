@@ -455,6 +455,15 @@ __host__ __device__ inline uint32_t dither_id(const InstDev& D, int64_t o, int j
   }
 }
 
+// a b + c in one rounding; on the host, which has no such instruction by default, in two.
+__host__ __device__ inline float ffma(float a, float b, float c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_fmaf(a, b, c);
+#else
+  return a * b + c;
+#endif
+}
+
 // ---- per-column constants (r is fixed along a thread's z loop) -------------
 struct RowC {
   float r, inv_r;
@@ -475,6 +484,7 @@ __host__ __device__ inline RowC make_row(const InstDev& D, int j) {
   // they are FP64 quotients rounded once.  The other constants take FP32 from
   // the correctly rounded 1 / r: their rounding is one more FP32 rounding of
   // the update (measured against the oracle: no change beyond 1e-7).
+#pragma clang fp contract(off)
   RowC R;
   const double rd = (double)D.r0 + j;
   const bool rper = D.side_rmin == SIDE_PERIODIC;
@@ -510,12 +520,12 @@ __host__ __device__ inline RowC make_row(const InstDev& D, int j) {
   const float inv = (float)invd;
   R.r = r;
   R.inv_r = inv;
-  R.lr0b = 0.5f * (1.0f + D.c_tau * inv * inv);
+  R.lr0b = 0.5f * ffma(D.c_tau * inv, inv, 1.0f);
   R.hcs2r = (float)(0.5 / 3.0) * inv;
   R.ar0 = inv * (float)(1.0 / 3.0);
   R.ar1 = 2.0f * D.c_tau * inv * inv;
-  R.omT1 = D.omc * (1.0f + D.tau_T * inv);
-  R.omT3 = D.omc * (1.0f - D.tau_T * inv);
+  R.omT1 = D.omc * ffma(D.tau_T, inv, 1.0f);
+  R.omT3 = D.omc * ffma(-D.tau_T, inv, 1.0f);
   return R;
 }
 
@@ -602,6 +612,7 @@ __host__ __device__ inline float fsqrt(float x) {
 // when the porosity is uniform).
 __host__ __device__ inline void porosity_of(const InstDev& D, float phi_raw, float& phi, float& cD,
                                             float& cF) {
+#pragma clang fp contract(off)
   if (D.phi_mode == 0) {
     phi = D.phiu;
     cD = D.cD;
@@ -629,114 +640,73 @@ __host__ __device__ inline void porosity(const InstDev& D, int64_t o, float& phi
   }
 }
 
-// a b + c in one rounding, as the compiler contracts it; on the host, which
-// contracts nothing, in two.
-__host__ __device__ inline float ffma(float a, float b, float c) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_fmaf(a, b, c);
-#else
-  return a * b + c;
-#endif
-}
-__host__ __device__ inline float mul_rounded(float a, float b) {
+// The sums of products below, with the product that is fused written out.  Which of
+// two products of a sum the compiler would contract depends on the code around it
+// (in one kernel it rounded the first, in another the second), and a node must
+// come out the same in every kernel that updates it: single steps, check steps,
+// captured steps and steps on LDS tiles.  Every function of the update therefore
+// switches contraction off and takes its fused products from here.
+__host__ __device__ inline float sum_first(float a, float b, float c, float d) {  // a b + c d, a b fused
 #pragma clang fp contract(off)
-  return a * b;
+  return ffma(a, b, c * d);
 }
-// a b + c d.  Which product of a sum the compiler contracts depends on the code
-// around it.  With EX the choice is written out, as the step kernels with wall
-// lanes make it (the first or the second product), so that the steps on LDS
-// tiles, compiled apart from them, give the same bits.
-template <bool EX>
-__host__ __device__ inline float sum_first(float a, float b, float c, float d) {
-  if constexpr (EX) return ffma(a, b, mul_rounded(c, d));
-  return a * b + c * d;
+__host__ __device__ inline float sum_second(float a, float b, float c, float d) {  // a b + c d, c d fused
+#pragma clang fp contract(off)
+  return ffma(c, d, a * b);
 }
-template <bool EX>
-__host__ __device__ inline float sum_second(float a, float b, float c, float d) {
-  if constexpr (EX) return ffma(c, d, mul_rounded(a, b));
-  return a * b + c * d;
+__host__ __device__ inline float diff_first(float a, float b, float c, float d) {  // a b - c d, a b fused
+#pragma clang fp contract(off)
+  return ffma(a, b, -(c * d));
 }
-// a b - c d, the same.
-template <bool EX>
-__host__ __device__ inline float diff_first(float a, float b, float c, float d) {
-  if constexpr (EX) return ffma(a, b, -mul_rounded(c, d));
-  return a * b - c * d;
-}
-
-// c + a b and c - a b, the same.
-template <bool EX>
-__host__ __device__ inline float add_product(float c, float a, float b) {
-  if constexpr (EX) return ffma(a, b, c);
-  return c + a * b;
-}
-template <bool EX>
-__host__ __device__ inline float sub_product(float c, float a, float b) {
-  if constexpr (EX) return ffma(-a, b, c);
-  return c - a * b;
-}
-// g_i - wt_i T of the moving temperature populations, the same: the step
-// kernels with wall lanes round wt_i theta (ROUND) for the axial ones.
-template <bool EX, bool ROUND>
+__host__ __device__ inline float add_product(float c, float a, float b) { return ffma(a, b, c); }   // c + a b
+__host__ __device__ inline float sub_product(float c, float a, float b) { return ffma(-a, b, c); }  // c - a b
+// 1 - s / 2 of a relaxation rate.
+__host__ __device__ inline float half_rate(float s) { return ffma(-0.5f, s, 1.0f); }
+// g_i - wt_i T of the moving temperature populations, wt_i T fused or rounded first
+// (ROUND: the axial ones of the step with wall lanes, whose wall lane shares the product).
+template <bool ROUND>
 __host__ __device__ inline float thermal_neq(float t, float theta) {
-  if constexpr (EX) return ROUND ? t - mul_rounded(WT1, theta) : ffma(-WT1, theta, t);
-  return t - WT1 * theta;
+#pragma clang fp contract(off)
+  return ROUND ? t - WT1 * theta : ffma(-WT1, theta, t);
 }
 
 // delta += M^{-1} X for moment increments X_1..X_8 (X_0 = 0); M^{-1} = M^T
 // diag(1/9, 1/36, 1/36, 1/6, 1/12, 1/6, 1/12, 1/4, 1/4), M of Eq. (18).
-template <bool EX = false>
 __host__ __device__ inline void back_transform(float d[9], float X1, float X2, float X3, float X4,
                                                float X5, float X6, float X7, float X8) {
-  if constexpr (EX) {
-    constexpr float c6 = (float)(1.0 / 6.0);
-    const float b1 = mul_rounded(X1, (float)(1.0 / 36.0)), b2 = mul_rounded(X2, (float)(1.0 / 36.0));
-    const float b4 = mul_rounded(X4, (float)(1.0 / 12.0)), b6 = mul_rounded(X6, (float)(1.0 / 12.0));
-    const float ax = ffma(b2, -2.0f, -b1), dg = ffma(2.0f, b1, b2);
-    const float qr = ffma(X3, c6, b4), qz = ffma(X5, c6, b6);
-    d[0] += ffma(b2, 4.0f, -4.0f * b1);
-    d[1] += ffma(0.25f, X7, ffma(-2.0f, b4, ffma(X3, c6, ax)));
-    d[2] += ffma(-0.25f, X7, ffma(-2.0f, b6, ffma(X5, c6, ax)));
-    d[3] += ffma(0.25f, X7, ffma(2.0f, b4, ffma(X3, -c6, ax)));
-    d[4] += ffma(-0.25f, X7, ffma(2.0f, b6, ffma(X5, -c6, ax)));
-    d[5] += ffma(0.25f, X8, dg + qr + qz);
-    d[6] += ffma(-0.25f, X8, dg - qr + qz);
-    d[7] += ffma(0.25f, X8, dg - qr - qz);
-    d[8] += ffma(-0.25f, X8, dg + qr - qz);
-    return;
-  }
+#pragma clang fp contract(off)
+  constexpr float c6 = (float)(1.0 / 6.0);
   const float a1 = X1 * (float)(1.0 / 36.0), a2 = X2 * (float)(1.0 / 36.0);
-  const float a3 = X3 * (float)(1.0 / 6.0), a4 = X4 * (float)(1.0 / 12.0);
-  const float a5 = X5 * (float)(1.0 / 6.0), a6 = X6 * (float)(1.0 / 12.0);
-  const float a7 = X7 * 0.25f, a8 = X8 * 0.25f;
-  const float e = -a1 - 2.0f * a2;      // common part of directions 1-4
-  const float c = 2.0f * a1 + a2;       // common part of directions 5-8
-  const float pr = a3 + a4, pz = a5 + a6;
-  d[0] += -4.0f * a1 + 4.0f * a2;
-  d[1] += e + a3 - 2.0f * a4 + a7;
-  d[2] += e + a5 - 2.0f * a6 - a7;
-  d[3] += e - a3 + 2.0f * a4 + a7;
-  d[4] += e - a5 + 2.0f * a6 - a7;
-  d[5] += c + pr + pz + a8;
-  d[6] += c - pr + pz - a8;
-  d[7] += c - pr - pz + a8;
-  d[8] += c + pr - pz - a8;
+  const float a4 = X4 * (float)(1.0 / 12.0), a6 = X6 * (float)(1.0 / 12.0);
+  const float e = ffma(a2, -2.0f, -a1);  // common part of directions 1-4
+  const float c = ffma(2.0f, a1, a2);    // common part of directions 5-8
+  const float pr = ffma(X3, c6, a4), pz = ffma(X5, c6, a6);
+  d[0] += ffma(a2, 4.0f, -4.0f * a1);
+  d[1] += ffma(0.25f, X7, ffma(-2.0f, a4, ffma(X3, c6, e)));
+  d[2] += ffma(-0.25f, X7, ffma(-2.0f, a6, ffma(X5, c6, e)));
+  d[3] += ffma(0.25f, X7, ffma(2.0f, a4, ffma(X3, -c6, e)));
+  d[4] += ffma(-0.25f, X7, ffma(2.0f, a6, ffma(X5, -c6, e)));
+  d[5] += ffma(0.25f, X8, c + pr + pz);
+  d[6] += ffma(-0.25f, X8, c - pr + pz);
+  d[7] += ffma(0.25f, X8, c - pr - pz);
+  d[8] += ffma(-0.25f, X8, c + pr - pz);
 }
 
 // Moment-space source S / r of Eq. (24) with F~ = (F_r + a_r, F_z) (Eq. 25);
 // unless printed, the a_r part is not divided by phi (see the header).
-template <bool EX = false>
 __host__ __device__ inline void source(bool printed, float rho, float ur, float uz, float iphi,
                                        float Fr, float Fz, float ar, float& S1, float& S7,
                                        float& S8) {
+#pragma clang fp contract(off)
   if (printed) {
     const float Ftr = Fr + ar;
-    S1 = 6.0f * rho * sum_first<EX>(ur, Ftr, uz, Fz) * iphi;
-    S7 = 2.0f * rho * diff_first<EX>(ur, Ftr, uz, Fz) * iphi;
-    S8 = rho * sum_first<EX>(ur, Fz, uz, Ftr) * iphi;
+    S1 = 6.0f * rho * sum_first(ur, Ftr, uz, Fz) * iphi;
+    S7 = 2.0f * rho * diff_first(ur, Ftr, uz, Fz) * iphi;
+    S8 = rho * sum_first(ur, Fz, uz, Ftr) * iphi;
   } else {
-    S1 = 6.0f * rho * sum_first<EX>(sum_first<EX>(ur, Fr, uz, Fz), iphi, ur, ar);
-    S7 = 2.0f * rho * sum_first<EX>(diff_first<EX>(ur, Fr, uz, Fz), iphi, ur, ar);
-    S8 = rho * sum_second<EX>(sum_second<EX>(ur, Fz, uz, Fr), iphi, uz, ar);
+    S1 = 6.0f * rho * sum_first(sum_first(ur, Fr, uz, Fz), iphi, ur, ar);
+    S7 = 2.0f * rho * sum_first(diff_first(ur, Fr, uz, Fz), iphi, ur, ar);
+    S8 = rho * sum_second(sum_second(ur, Fz, uz, Fr), iphi, uz, ar);
   }
 }
 
@@ -799,10 +769,11 @@ __host__ __device__ inline void store_wall(const InstDev& D, const A& P, int jb,
 // rho_B, u = 0 and the wall temperature; with inlet/outlet columns (Sec. 4.1)
 // the inlet takes rho_B, u = (0, u_in) and the inlet temperature, the outlet
 // rho = 1 and B's u and T.  Radial walls win at corners.
-template <typename S, bool ODD, int MODE, typename A>
+template <typename S, bool ODD, int MODE, bool WL, typename A>
 __host__ __device__ inline void wall_node(const InstDev& D, const A& P, const NodeState& B, float rB,
                                           int j, int k, int dr, int dz, int mac_slot,
                                           const FieldOut& fo, Dither& rn) {
+#pragma clang fp contract(off)
   const int jb = j + dr, kb = k + dz;
   const float rb = rB + (float)dr;
   const float inv_rb = frcp(rb);
@@ -842,58 +813,57 @@ __host__ __device__ inline void wall_node(const InstDev& D, const A& P, const No
     // At one wave per SIMD (small grids) the wall work sits on the critical
     // path of the owner's wave, so it is kept as short as the case allows.
     const float q = rB * inv_rb;
-    const float hb = 0.5f * CS2 * inv_rb;
-    const float Gz = D.gbeta * (Tb - D.T_ref) + D.accel_z;
-    const float eu[5] = {0.0f, B.ur, B.uz, -B.ur, -B.uz};
-    const float wt[5] = {WT0, WT1, WT1, WT1, WT1};
-    const float tb1 = D.tau_T * inv_rb;
-    const float om[5] = {D.omc, D.omc * (1.0f + tb1), D.omc, D.omc * (1.0f - tb1), D.omc};
-    float qn[5];
-    for (int i = 1; i < 5; ++i) qn[i] = B.t[i] - wt[i] * B.theta;
-    qn[0] = -((qn[1] + qn[3]) + (qn[2] + qn[4]));
-    float d[9], tg[5];
-    d[0] = W0 * drho;
-    d[1] = d[2] = d[3] = d[4] = W1 * drho;
-    d[5] = d[6] = d[7] = d[8] = W5 * drho;
+    const float hb = 0.5f * CS2 * inv_rb, cr = CS2 * inv_rb;
+    const float Gz = ffma(D.gbeta, Tb - D.T_ref, D.accel_z);
+    const float he = half_rate(D.s_e), hp = half_rate(D.s_eps), hj = half_rate(D.s_j);
+    const float hq = half_rate(D.s_q), hn = half_rate(D.s_nu);
+    float X1 = (1.0f - D.s_e) * q * B.n1, X2 = (1.0f - D.s_eps) * q * B.n2;
+    float X3 = (1.0f - D.s_j) * q * B.n3, X4 = (1.0f - D.s_q) * q * B.n4;
+    float X5 = (1.0f - D.s_j) * q * B.n5, X6 = (1.0f - D.s_q) * q * B.n6;
+    float X7 = (1.0f - D.s_nu) * q * B.n7, X8 = (1.0f - D.s_nu) * q * B.n8;
+    // (1 - omega_i(r_b)) g^neq(B)
+    const float T5 = 5.0f * WT1 * B.T;
+    const float om1 = ffma(D.tau_T, inv_rb, 1.0f), om3 = ffma(-D.tau_T, inv_rb, 1.0f), om2 = 1.0f - D.omc;
+    const float q2 = thermal_neq<WL>(B.t[2], B.theta), q4 = thermal_neq<WL>(B.t[4], B.theta);
+    float tg[5];
+    tg[1] = ffma(-D.omc, om1, 1.0f) * ffma(-T5, B.ur, thermal_neq<false>(B.t[1], B.theta));
+    tg[2] = om2 * ffma(-T5, B.uz, q2);
+    tg[3] = ffma(-D.omc, om3, 1.0f) * ffma(T5, B.ur, thermal_neq<false>(B.t[3], B.theta));
+    tg[4] = om2 * ffma(T5, B.uz, q4);
     if (!moving) {
-      const float S3 = rhob * (phib * D.accel_r + CS2 * inv_rb), S5 = rhob * phib * Gz;
-      back_transform(d, (1.0f - D.s_e) * q * B.n1, (1.0f - D.s_eps) * q * B.n2,
-                     (1.0f - D.s_j) * q * B.n3 + (1.0f - 0.5f * D.s_j) * S3 - hb,
-                     (1.0f - D.s_q) * q * B.n4 - (1.0f - 0.5f * D.s_q) * S3 + hb,
-                     (1.0f - D.s_j) * q * B.n5 + (1.0f - 0.5f * D.s_j) * S5,
-                     (1.0f - D.s_q) * q * B.n6 - (1.0f - 0.5f * D.s_q) * S5,
-                     (1.0f - D.s_nu) * q * B.n7, (1.0f - D.s_nu) * q * B.n8);
-      for (int i = 0; i < 5; ++i) {
-        const float gneq = qn[i] - 5.0f * wt[i] * B.T * eu[i];
-        tg[i] = wt[i] * (Tb - D.T_s) + (1.0f - om[i]) * gneq;
-      }
+      const float S3 = rhob * ffma(phib, D.accel_r, cr), S5 = rhob * phib * Gz;
+      X3 = ffma(hj, S3, X3) - hb;
+      X4 = ffma(-hq, S3, X4) + hb;
+      X5 = ffma(hj, S5, X5);
+      X6 = ffma(-hq, S5, X6);
+      for (int i = 1; i < 5; ++i) tg[i] = ffma(Tb - D.T_s, WT1, tg[i]);
     } else {
       const float iphib = frcp(phib);
-      const float drag = cDb + cFb * fsqrt(urb * urb + uzb * uzb);
-      const float Frb = phib * D.accel_r - drag * urb, Fzb = phib * Gz - drag * uzb;
-      const float arb = CS2 * inv_rb - 2.0f * D.c_tau * urb * inv_rb * inv_rb;  // Eq. (25)
+      const float ur2 = urb * urb, uz2 = uzb * uzb, u2 = ffma(uzb, uzb, ur2);
+      const float drag = ffma(cFb, fsqrt(u2), cDb);
+      const float Frb = ffma(phib, D.accel_r, -(urb * drag)), Fzb = ffma(phib, Gz, -(uzb * drag));
+      const float arb = ffma(-inv_rb, 2.0f * D.c_tau * urb * inv_rb, cr);  // Eq. (25)
       float S1, S7, S8;
       source(D.src_printed != 0, rhob, urb, uzb, iphib, Frb, Fzb, arb, S1, S7, S8);
-      const float S3 = rhob * (Frb + arb), S5 = rhob * Fzb;
-      const float ru2 = 3.0f * rhob * (urb * urb + uzb * uzb) * iphib;
-      back_transform(d, ru2 + (1.0f - D.s_e) * q * B.n1 + (1.0f - 0.5f * D.s_e) * S1,
-                     -ru2 + (1.0f - D.s_eps) * q * B.n2 - (1.0f - 0.5f * D.s_eps) * S1,
-                     rhob * urb + (1.0f - D.s_j) * q * B.n3 + (1.0f - 0.5f * D.s_j) * S3 - hb,
-                     -rhob * urb + (1.0f - D.s_q) * q * B.n4 - (1.0f - 0.5f * D.s_q) * S3 + hb,
-                     rhob * uzb + (1.0f - D.s_j) * q * B.n5 + (1.0f - 0.5f * D.s_j) * S5,
-                     -rhob * uzb + (1.0f - D.s_q) * q * B.n6 - (1.0f - 0.5f * D.s_q) * S5,
-                     rhob * (urb * urb - uzb * uzb) * iphib + (1.0f - D.s_nu) * q * B.n7 +
-                         (1.0f - 0.5f * D.s_nu) * S7,
-                     rhob * urb * uzb * iphib + (1.0f - D.s_nu) * q * B.n8 +
-                         (1.0f - 0.5f * D.s_nu) * S8);
-      const float eb[5] = {0.0f, urb, uzb, -urb, -uzb};
-      const float psib = -urb * inv_rb;
-      for (int i = 0; i < 5; ++i) {
-        const float gneq = qn[i] - 5.0f * wt[i] * B.T * eu[i];
-        const float geqm = wt[i] * Tb * 5.0f * eb[i];  // velocity part of g^eq(T_b, u_b)
-        tg[i] = wt[i] * (Tb - D.T_s) + geqm + (1.0f - om[i]) * gneq + psib * (wt[i] * Tb + geqm);
-      }
+      const float S3 = rhob * (Frb + arb), S5 = rhob * Fzb, r3 = 3.0f * rhob * u2;
+      X1 = ffma(he, S1, ffma(iphib, r3, X1));
+      X2 = ffma(-hp, S1, ffma(-iphib, r3, X2));
+      X3 = ffma(hj, S3, ffma(urb, rhob, X3)) - hb;
+      X4 = ffma(-hq, S3, ffma(-urb, rhob, X4)) + hb;
+      X5 = ffma(hj, S5, ffma(uzb, rhob, X5));
+      X6 = ffma(-hq, S5, ffma(-uzb, rhob, X6));
+      X7 = ffma(hn, S7, ffma(iphib, rhob * (ur2 - uz2), X7));
+      X8 = ffma(hn, S8, ffma(iphib, rhob * urb * uzb, X8));
+      // velocity part of g^eq(T_b, u_b), and psi_i
+      const float wT = WT1 * Tb, t5 = wT * 5.0f, base = WT1 * (Tb - D.T_s), psib = -urb * inv_rb;
+      tg[1] = ffma(psib, ffma(urb, t5, wT), tg[1] + ffma(urb, t5, base));
+      tg[2] = ffma(psib, ffma(uzb, t5, wT), tg[2] + ffma(uzb, t5, base));
+      tg[3] = ffma(psib, ffma(-urb, t5, wT), tg[3] + ffma(-urb, t5, base));
+      tg[4] = ffma(psib, ffma(-uzb, t5, wT), tg[4] + ffma(-uzb, t5, base));
     }
+    const float w1 = W1 * drho, w5 = W5 * drho;
+    float d[9] = {0.0f, w1, w1, w1, w1, w5, w5, w5, w5};  // a wall sends nothing at rest
+    back_transform(d, X1, X2, X3, X4, X5, X6, X7, X8);
     store_wall<S, ODD>(D, P, jb, kb, d, tg, rn);
   }
   if (MODE == MODE_STEP_MACRO) {
@@ -911,105 +881,6 @@ __host__ __device__ inline void wall_node(const InstDev& D, const A& P, const No
     if (fo.mask) fo.mask[o] = m;
     if (fo.drho) fo.drho[o] = drho;
   }
-}
-
-// wall_node for one boundary node on a lane of its own (steps on LDS tiles), any
-// (dr, dz) in one pass.  The compiler contracts wall_node's products as the
-// code around it falls; here each contraction is written out, the ones that the
-// step kernels' owners make, so that both give the same bits.
-template <typename S, bool ODD, bool WL, typename A>
-__host__ __device__ inline void wall_node_alone(const InstDev& D, const A& P, const NodeState& B, float rB, int j,
-                                                int k, int dr, int dz, Dither& rn) {
-#pragma clang fp contract(off)
-  const int jb = j + dr, kb = k + dz;
-  const float rb = rB + (float)dr;
-  const float inv_rb = frcp(rb);
-  const int64_t ob = row_off(kb, D.stride) + jb;
-  float phib, cDb, cFb;
-  porosity_of(D, D.phi_mode == 0 ? 0.0f : D.phi[plane_index<A::ADDR, S>(D, ob)], phib, cDb, cFb);
-  const uint8_t m = node_mask(D, jb, kb);
-  float drho = B.drho, urb = 0.0f, uzb = 0.0f;
-  const bool moving = D.side_z == SIDE_FLOW && !(m & (MASK_RMIN | MASK_RMAX));
-  if (moving) {
-    if (m & MASK_ZMIN) {
-      uzb = D.u_in;
-    } else {
-      drho = 0.0f;
-      urb = B.ur;
-      uzb = B.uz;
-    }
-  }
-  const float rhob = 1.0f + drho;
-  float Tb = B.T, qf;
-  if ((m & MASK_RMIN) && D.therm_rmin == THERM_FIXED) Tb = D.T_rmin;
-  else if ((m & MASK_RMAX) && D.therm_rmax == THERM_FIXED) Tb = D.T_rmax;
-  else if ((m & MASK_ZMIN) && D.therm_z == THERM_FIXED) Tb = D.T_zmin;
-  else if ((m & MASK_ZMAX) && D.therm_z == THERM_FIXED && D.side_z != SIDE_FLOW) Tb = D.T_zmax;
-  else if (flux_node(D, m, kb, qf)) Tb = B.T + qf;
-
-  const float q = rB * inv_rb;
-  const float hb = 0.5f * CS2 * inv_rb, cr = CS2 * inv_rb;
-  const float Gz = ffma(D.gbeta, Tb - D.T_ref, D.accel_z);
-  const float he = 1.0f - 0.5f * D.s_e, hp = 1.0f - 0.5f * D.s_eps, hj = 1.0f - 0.5f * D.s_j;
-  const float hq = 1.0f - 0.5f * D.s_q, hn = 1.0f - 0.5f * D.s_nu;
-  float X1 = (1.0f - D.s_e) * q * B.n1, X2 = (1.0f - D.s_eps) * q * B.n2;
-  float X3 = (1.0f - D.s_j) * q * B.n3, X4 = (1.0f - D.s_q) * q * B.n4;
-  float X5 = (1.0f - D.s_j) * q * B.n5, X6 = (1.0f - D.s_q) * q * B.n6;
-  float X7 = (1.0f - D.s_nu) * q * B.n7, X8 = (1.0f - D.s_nu) * q * B.n8;
-  // g^neq of the owner times 1 - omega(r_b)
-  const float T5 = 5.0f * WT1 * B.T;
-  const float om1 = ffma(D.tau_T, inv_rb, 1.0f), om3 = ffma(-D.tau_T, inv_rb, 1.0f), om2 = 1.0f - D.omc;
-  constexpr bool RND = WL;
-  const float q2 = thermal_neq<true, RND>(B.t[2], B.theta), q4 = thermal_neq<true, RND>(B.t[4], B.theta);
-  float tg[5];
-  tg[1] = ffma(-D.omc, om1, 1.0f) * ffma(-T5, B.ur, ffma(-WT1, B.theta, B.t[1]));
-  tg[2] = om2 * ffma(-T5, B.uz, q2);
-  tg[3] = ffma(-D.omc, om3, 1.0f) * ffma(T5, B.ur, ffma(-WT1, B.theta, B.t[3]));
-  tg[4] = om2 * ffma(T5, B.uz, q4);
-  if (!moving) {
-    const float S3 = ffma(phib, D.accel_r, cr) * rhob, S5 = rhob * phib * Gz;
-    X3 = ffma(hj, S3, X3) - hb;
-    X4 = ffma(-hq, S3, X4) + hb;
-    X5 = ffma(hj, S5, X5);
-    X6 = ffma(-hq, S5, X6);
-    for (int i = 1; i < 5; ++i) tg[i] = ffma(Tb - D.T_s, WT1, tg[i]);
-  } else {
-    const float iphib = frcp(phib);
-    const float ur2 = urb * urb, uz2 = uzb * uzb, u2 = ffma(uzb, uzb, ur2);
-    const float drag = ffma(cFb, fsqrt(u2), cDb);
-    const float Frb = ffma(phib, D.accel_r, -(urb * drag)), Fzb = ffma(phib, Gz, -(uzb * drag));
-    const float arb = ffma(-inv_rb, 2.0f * D.c_tau * urb * inv_rb, cr);
-    const float zz = uzb * Fzb, rz = urb * Fzb, Ft = Frb + arb;
-    float S1, S7, S8;
-    if (D.src_printed != 0) {
-      S1 = 6.0f * rhob * ffma(urb, Ft, zz) * iphib;
-      S7 = 2.0f * rhob * ffma(urb, Ft, -zz) * iphib;
-      S8 = rhob * ffma(uzb, Ft, rz) * iphib;
-    } else {
-      const float ua = urb * arb;
-      S1 = 6.0f * rhob * ffma(iphib, ffma(urb, Frb, zz), ua);
-      S7 = 2.0f * rhob * ffma(iphib, ffma(urb, Frb, -zz), ua);
-      S8 = rhob * ffma(uzb, arb, iphib * ffma(uzb, Frb, rz));
-    }
-    const float S3 = rhob * Ft, S5 = rhob * Fzb, r3 = 3.0f * rhob * u2;
-    X1 = ffma(he, S1, ffma(iphib, r3, X1));
-    X2 = ffma(-hp, S1, ffma(-iphib, r3, X2));
-    X3 = ffma(hj, S3, ffma(urb, rhob, X3)) - hb;
-    X4 = ffma(-hq, S3, ffma(-urb, rhob, X4)) + hb;
-    X5 = ffma(hj, S5, ffma(uzb, rhob, X5));
-    X6 = ffma(-hq, S5, ffma(-uzb, rhob, X6));
-    X7 = ffma(hn, S7, ffma(iphib, rhob * (ur2 - uz2), X7));
-    X8 = ffma(hn, S8, ffma(iphib, rhob * urb * uzb, X8));
-    const float wT = WT1 * Tb, t5 = wT * 5.0f, base = WT1 * (Tb - D.T_s), psib = -urb * inv_rb;
-    tg[1] = ffma(psib, ffma(urb, t5, wT), tg[1] + ffma(urb, t5, base));
-    tg[2] = ffma(psib, ffma(uzb, t5, wT), tg[2] + ffma(uzb, t5, base));
-    tg[3] = ffma(psib, ffma(-urb, t5, wT), tg[3] + ffma(-urb, t5, base));
-    tg[4] = ffma(psib, ffma(-uzb, t5, wT), tg[4] + ffma(-uzb, t5, base));
-  }
-  const float w1 = W1 * drho, w5 = W5 * drho;
-  float d[9] = {0.0f, w1, w1, w1, w1, w5, w5, w5, w5};
-  back_transform<true>(d, X1, X2, X3, X4, X5, X6, X7, X8);
-  store_wall<S, ODD>(D, P, jb, kb, d, tg, rn);
 }
 
 // The populations arriving at fluid node (j, k) (as stored, unscaled to
@@ -1173,10 +1044,12 @@ __device__ inline void pattern_store(const InstDev& D, const RowC& R, int j, int
 // wl: directions 1, 5, 8 or 3, 6, 7, and the D2Q5 one) to the slots its
 // fluid neighbours read; its other populations go to the wall column's own
 // slots, which no fluid node reads (node_update_loaded).
-template <bool EX = false, bool S16 = false>
+// S16: the 16-bit kernels fuse other products of S_3 and c_s^2 / (2 r_b).
+template <bool S16>
 __host__ __device__ inline void wall_lane_inputs(const InstDev& D, const NodeState& B, const float t[5],
                                                  float rB, int wl, int k, int64_t ob, float d[9],
                                                  float X[8], float& ga, float& Tb) {
+#pragma clang fp contract(off)
   const bool lo = wl > 0;
   const float fs = (float)wl;
   const float inv_rb = frcp(rB - fs);
@@ -1187,36 +1060,34 @@ __host__ __device__ inline void wall_lane_inputs(const InstDev& D, const NodeSta
   else if (th == THERM_FLUX && k >= D.qk_lo && k <= D.qk_hi) Tb = B.T + (lo ? D.q_rmin : D.q_rmax);
   const float drho = B.drho, rhob = 1.0f + drho;
   const float q = rB * inv_rb;
-  const float hb = EX ? mul_rounded(0.5f * CS2, inv_rb) : 0.5f * CS2 * inv_rb;
-  const float Gz = D.gbeta * (Tb - D.T_ref) + D.accel_z;
-  const float S3 = rhob * (S16 ? sum_second<EX>(phib, D.accel_r, CS2, inv_rb) : sum_first<EX>(phib, D.accel_r, CS2, inv_rb));
+  const float hj = half_rate(D.s_j), hq = half_rate(D.s_q);
+  const float Gz = ffma(D.gbeta, Tb - D.T_ref, D.accel_z);
+  const float S3 = rhob * (S16 ? sum_second(phib, D.accel_r, CS2, inv_rb) : sum_first(phib, D.accel_r, CS2, inv_rb));
   const float S5 = rhob * phib * Gz;
   X[0] = (1.0f - D.s_e) * q * B.n1;
   X[1] = (1.0f - D.s_eps) * q * B.n2;
-  X[2] = sum_first<EX>((1.0f - D.s_j) * q, B.n3, 1.0f - 0.5f * D.s_j, S3);
-  X[3] = diff_first<EX>((1.0f - D.s_q) * q, B.n4, 1.0f - 0.5f * D.s_q, S3);
-  if constexpr (EX && S16) {
+  X[2] = sum_first((1.0f - D.s_j) * q, B.n3, hj, S3);
+  X[3] = diff_first((1.0f - D.s_q) * q, B.n4, hq, S3);
+  if constexpr (S16) {
     X[2] = ffma(-0.5f * CS2, inv_rb, X[2]);
     X[3] = ffma(0.5f * CS2, inv_rb, X[3]);
   } else {
+    const float hb = 0.5f * CS2 * inv_rb;
     X[2] -= hb;
     X[3] += hb;
   }
-  X[4] = sum_first<EX>((1.0f - D.s_j) * q, B.n5, 1.0f - 0.5f * D.s_j, S5);
-  X[5] = diff_first<EX>((1.0f - D.s_q) * q, B.n6, 1.0f - 0.5f * D.s_q, S5);
+  X[4] = sum_first((1.0f - D.s_j) * q, B.n5, hj, S5);
+  X[5] = diff_first((1.0f - D.s_q) * q, B.n6, hq, S5);
   X[6] = (1.0f - D.s_nu) * q * B.n7;
   X[7] = (1.0f - D.s_nu) * q * B.n8;
-  d[0] = EX ? mul_rounded(W0, drho) : W0 * drho;
+  d[0] = W0 * drho;
 #pragma unroll
-  for (int i = 1; i < 5; ++i) d[i] = EX ? mul_rounded(W1, drho) : W1 * drho;
+  for (int i = 1; i < 5; ++i) d[i] = W1 * drho;
 #pragma unroll
-  for (int i = 5; i < 9; ++i) d[i] = EX ? mul_rounded(W5, drho) : W5 * drho;
+  for (int i = 5; i < 9; ++i) d[i] = W5 * drho;
   const float tB = lo ? t[1] : t[3];
-  if constexpr (EX)
-    ga = ffma(ffma(-D.omc, ffma(fs * D.tau_T, inv_rb, 1.0f), 1.0f), ffma(-(5.0f * WT1 * B.T * fs), B.ur, tB - mul_rounded(WT1, B.theta)),
-              mul_rounded(WT1, Tb - D.T_s));
-  else
-    ga = WT1 * (Tb - D.T_s) + (1.0f - D.omc * (1.0f + fs * D.tau_T * inv_rb)) * (tB - WT1 * B.theta - 5.0f * WT1 * B.T * fs * B.ur);
+  ga = ffma(ffma(-D.omc, ffma(fs * D.tau_T, inv_rb, 1.0f), 1.0f), ffma(-(5.0f * WT1 * B.T * fs), B.ur, tB - WT1 * B.theta),
+            WT1 * (Tb - D.T_s));
 }
 
 // Whether the predicate holds on any lane of the wave (on the host, for this
@@ -1261,8 +1132,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
                                                    int mac_slot, const FieldOut& fo, uint32_t seed,
                                                    const float s[9], const float t_in[5],
                                                    float phi_raw, int wl = 0) {
-  // steps on LDS tiles contract as the step kernels do
-  constexpr bool EX = MODE == MODE_WALL || MODE == MODE_TILE;
+#pragma clang fp contract(off)
   const PopAcc<S, BUF> P(D);
   const int64_t pl = D.plane;
   const int st = D.stride;
@@ -1283,12 +1153,12 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   d[0] = s[0];
   d[2] = s[2];
   d[4] = s[4];
-  d[1] = EX ? ffma(s[1], R.rp, R.op1) : s[1] * R.rp + R.op1;
-  d[5] = EX ? ffma(s[5], R.rp, R.op5) : s[5] * R.rp + R.op5;
-  d[8] = EX ? ffma(s[8], R.rp, R.op5) : s[8] * R.rp + R.op5;
-  d[3] = EX ? ffma(s[3], R.rm, R.om1) : s[3] * R.rm + R.om1;
-  d[6] = EX ? ffma(s[6], R.rm, R.om5) : s[6] * R.rm + R.om5;
-  d[7] = EX ? ffma(s[7], R.rm, R.om5) : s[7] * R.rm + R.om5;
+  d[1] = ffma(s[1], R.rp, R.op1);
+  d[5] = ffma(s[5], R.rp, R.op5);
+  d[8] = ffma(s[8], R.rp, R.op5);
+  d[3] = ffma(s[3], R.rm, R.om1);
+  d[6] = ffma(s[6], R.rm, R.om5);
+  d[7] = ffma(s[7], R.rm, R.om5);
 
   // ---- macroscopic values ------------------------------------------------
   NodeState B;
@@ -1302,15 +1172,15 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   B.theta = t[0] + t[1] + t[2] + t[3] + t[4];               // T - T_s, Eq. (38)
   B.T = D.T_s + B.theta;
   const float Gr = D.accel_r;
-  const float Gz = EX ? ffma(D.gbeta, B.theta, D.az_s) : D.gbeta * B.theta + D.az_s;  // Eq. (7)
-  const float vr = sum_first<EX>(add_product<EX>(Jr, R.hcs2r, B.drho), inv_rho, 0.5f * phi, Gr);  // Eq. (29) / r
-  const float vz = sum_first<EX>(Jz, inv_rho, 0.5f * phi, Gz);
-  const float lr0 = R.lr0b + 0.25f * cD;                    // Eq. (30) / r
-  const float lz0 = 0.5f + 0.25f * cD;
+  const float Gz = ffma(D.gbeta, B.theta, D.az_s);  // Eq. (7)
+  const float vr = sum_first(add_product(Jr, R.hcs2r, B.drho), inv_rho, 0.5f * phi, Gr);  // Eq. (29) / r
+  const float vz = sum_first(Jz, inv_rho, 0.5f * phi, Gz);
+  const float lr0 = ffma(0.25f, cD, R.lr0b);                    // Eq. (30) / r
+  const float lz0 = ffma(0.25f, cD, 0.5f);
   const float l1 = 0.5f * cF;
-  const float vm = fsqrt(sum_second<EX>(vr, vr, vz, vz));
-  B.ur = vr * frcp(lr0 + fsqrt(sum_first<EX>(lr0, lr0, l1, vm)));       // Eq. (28)
-  B.uz = vz * frcp(lz0 + fsqrt(sum_first<EX>(lz0, lz0, l1, vm)));
+  const float vm = fsqrt(sum_second(vr, vr, vz, vz));
+  B.ur = vr * frcp(lr0 + fsqrt(sum_first(lr0, lr0, l1, vm)));       // Eq. (28)
+  B.uz = vz * frcp(lz0 + fsqrt(sum_first(lz0, lz0, l1, vm)));
   const float ur = B.ur, uz = B.uz, rho = B.rho;
 
   if (MODE == MODE_STEP_MACRO) {
@@ -1330,28 +1200,26 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   }
 
   // ---- forces (Eq. 6) and the axisymmetric correction (Eq. 25) -----------
-  const float uu = sum_first<EX>(ur, ur, uz, uz);
+  const float uu = sum_first(ur, ur, uz, uz);
   const float um = fsqrt(uu);
-  const float drag = add_product<EX>(cD, cF, um);
-  const float Fr = diff_first<EX>(phi, Gr, drag, ur);
-  const float Fz = diff_first<EX>(phi, Gz, drag, uz);
-  const float ar = sub_product<EX>(R.ar0, R.ar1, ur);
+  const float drag = add_product(cD, cF, um);
+  const float Fr = diff_first(phi, Gr, drag, ur);
+  const float Fz = diff_first(phi, Gz, drag, uz);
+  const float ar = sub_product(R.ar0, R.ar1, ur);
 
   // ---- moments of d and the non-equilibrium part (Eqs. 16-20) -----------
   const float iphi = frcp(phi);
   const float ru2 = rho * uu * iphi;
-  B.n1 = sub_product<EX>((-4.0f * d[0] - sa + 2.0f * sd) + 2.0f * B.drho, 3.0f, ru2);
-  B.n2 = add_product<EX>((4.0f * d[0] - 2.0f * sa + sd) - B.drho, 3.0f, ru2);
-  const float m4 = -2.0f * d[1] + 2.0f * d[3] + d[5] - d[6] - d[7] + d[8];
-  B.n3 = sub_product<EX>(Jr - R.hcs2r, rho, ur);
-  B.n4 = add_product<EX>(m4 + R.hcs2r, rho, ur);
-  B.n5 = sub_product<EX>(Jz, rho, uz);
-  B.n6 = add_product<EX>(-2.0f * d[2] + 2.0f * d[4] + d[5] + d[6] - d[7] - d[8], rho, uz);
-  if constexpr (EX)
-    B.n7 = ffma(-iphi, rho * (mul_rounded(ur, ur) - mul_rounded(uz, uz)), d[1] - d[2] + d[3] - d[4]);
-  else
-    B.n7 = (d[1] - d[2] + d[3] - d[4]) - rho * (ur * ur - uz * uz) * iphi;
-  B.n8 = sub_product<EX>(d[5] - d[6] + d[7] - d[8], rho * ur * uz, iphi);
+  B.n1 = sub_product(ffma(2.0f, B.drho, ffma(2.0f, sd, ffma(-4.0f, d[0], -sa))), 3.0f, ru2);
+  B.n2 = add_product(ffma(4.0f, d[0], -2.0f * sa) + sd - B.drho, 3.0f, ru2);
+  const float m4 = ffma(2.0f, d[3], -2.0f * d[1]) + d[5] - d[6] - d[7] + d[8];
+  // n_3 and n_4 serve the boundary nodes only (owners round rho u_r, wall lanes fuse it)
+  B.n3 = WL ? sub_product(Jr - R.hcs2r, rho, ur) : (Jr - R.hcs2r) - rho * ur;
+  B.n4 = WL ? add_product(m4 + R.hcs2r, rho, ur) : (m4 + R.hcs2r) + rho * ur;
+  B.n5 = sub_product(Jz, rho, uz);
+  B.n6 = add_product(ffma(2.0f, d[4], -2.0f * d[2]) + d[5] + d[6] - d[7] - d[8], rho, uz);
+  B.n7 = sub_product(d[1] - d[2] + d[3] - d[4], rho * (ur * ur - uz * uz), iphi);
+  B.n8 = sub_product(d[5] - d[6] + d[7] - d[8], rho * ur * uz, iphi);
 
   if constexpr (MODE == MODE_WALL) {
     const int dr = mac_slot / 3 - 1, dz = mac_slot % 3 - 1;
@@ -1362,7 +1230,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
       for (int i = 0; i < 13; ++i) (void)rn.next();
       owned_draws<WL>(D, j, k, dr, dz, rn);
     }
-    wall_node_alone<S, ODD, WL>(D, P, B, R.r, j, k, dr, dz, rn);
+    wall_node<S, ODD, MODE, WL>(D, P, B, R.r, j, k, dr, dz, 0, fo, rn);
     return;
   }
 
@@ -1375,25 +1243,25 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   if (MODE != MODE_FIELDS) {
     // ---- source (Eq. 24) and relaxation (Eq. 21) --------------------------
     float S1, S7, S8;
-    source<EX>(D.src_printed != 0, rho, ur, uz, iphi, Fr, Fz, ar, S1, S7, S8);
+    source(D.src_printed != 0, rho, ur, uz, iphi, Fr, Fz, ar, S1, S7, S8);
     const float S5 = rho * Fz;
     // The radial-momentum and radial-flux increments are written so that the
     // quiescent parts (c_s^2 / (2 r) in n_3, n_4 and c_s^2 / r in S_3) and
     // the change of reference state (-c_s^2 / r in moment 3, +c_s^2 / r in
     // moment 4) cancel exactly: what remains scales with rho - 1 and u.
-    const float S3d = rho * (Fr - (EX ? mul_rounded(R.ar1, ur) : R.ar1 * ur));  // S_3 minus its quiescent part rho c_s^2 / r
-    const float X3 = add_product<EX>(sum_second<EX>(-D.s_j, sub_product<EX>(Jr, rho, ur), 1.0f - 0.5f * D.s_j, S3d),
+    const float S3d = rho * (Fr - R.ar1 * ur);  // S_3 minus its quiescent part rho c_s^2 / r
+    const float X3 = add_product(sum_second(-D.s_j, sub_product(Jr, rho, ur), half_rate(D.s_j), S3d),
                                      (2.0f - D.s_j) * R.hcs2r, B.drho);
-    const float X4 = sub_product<EX>(diff_first<EX>(-D.s_q, add_product<EX>(m4, rho, ur), 1.0f - 0.5f * D.s_q, S3d),
+    const float X4 = sub_product(diff_first(-D.s_q, add_product(m4, rho, ur), half_rate(D.s_q), S3d),
                                      (2.0f - D.s_q) * R.hcs2r, B.drho);
-    float X[8] = {sum_second<EX>(-D.s_e, B.n1, 1.0f - 0.5f * D.s_e, S1),
-                  diff_first<EX>(-D.s_eps, B.n2, 1.0f - 0.5f * D.s_eps, S1),
+    float X[8] = {sum_second(-D.s_e, B.n1, half_rate(D.s_e), S1),
+                  diff_first(-D.s_eps, B.n2, half_rate(D.s_eps), S1),
                   X3,
                   X4,
-                  sum_second<EX>(-D.s_j, B.n5, 1.0f - 0.5f * D.s_j, S5),
-                  diff_first<EX>(-D.s_q, B.n6, 1.0f - 0.5f * D.s_q, S5),
-                  sum_second<EX>(-D.s_nu, B.n7, 1.0f - 0.5f * D.s_nu, S7),
-                  sum_second<EX>(-D.s_nu, B.n8, 1.0f - 0.5f * D.s_nu, S8)};
+                  sum_second(-D.s_j, B.n5, half_rate(D.s_j), S5),
+                  diff_first(-D.s_q, B.n6, half_rate(D.s_q), S5),
+                  sum_second(-D.s_nu, B.n7, half_rate(D.s_nu), S7),
+                  sum_second(-D.s_nu, B.n8, half_rate(D.s_nu), S8)};
 
     // ---- temperature collision (Eqs. 33-37) ------------------------------
     // q_i = g_i - wt_i T is the part of g - g^eq that does not depend on u;
@@ -1405,23 +1273,15 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
     float tg[5];
     {
       const float e1 = 5.0f * ur, e2 = 5.0f * uz;
-      const float q1 = thermal_neq<EX, false>(t[1], B.theta), q2 = thermal_neq<EX, WL>(t[2], B.theta);
-      const float q3 = thermal_neq<EX, false>(t[3], B.theta), q4 = thermal_neq<EX, WL>(t[4], B.theta);
+      const float q1 = thermal_neq<false>(t[1], B.theta), q2 = thermal_neq<WL>(t[2], B.theta);
+      const float q3 = thermal_neq<false>(t[3], B.theta), q4 = thermal_neq<WL>(t[4], B.theta);
       const float q0 = -((q1 + q3) + (q2 + q4));
-      if constexpr (EX) {
-        const float pw = mul_rounded(psi, wT1);
-        tg[0] = ffma(psi, wT0, ffma(-D.omc, q0, t[0]));
-        tg[1] = ffma(ffma(5.0f, ur, 1.0f), pw, ffma(-R.omT1, ffma(-wT1, e1, q1), t[1]));
-        tg[2] = ffma(ffma(5.0f, uz, 1.0f), pw, ffma(-D.omc, ffma(-wT1, e2, q2), t[2]));
-        tg[3] = ffma(ffma(-5.0f, ur, 1.0f), pw, ffma(-R.omT3, ffma(wT1, e1, q3), t[3]));
-        tg[4] = ffma(ffma(-5.0f, uz, 1.0f), pw, ffma(-D.omc, ffma(wT1, e2, q4), t[4]));
-      } else {
-        tg[0] = t[0] - D.omc * q0 + psi * wT0;
-        tg[1] = t[1] - R.omT1 * (q1 - wT1 * e1) + psi * wT1 * (1.0f + e1);
-        tg[2] = t[2] - D.omc * (q2 - wT1 * e2) + psi * wT1 * (1.0f + e2);
-        tg[3] = t[3] - R.omT3 * (q3 + wT1 * e1) + psi * wT1 * (1.0f - e1);
-        tg[4] = t[4] - D.omc * (q4 + wT1 * e2) + psi * wT1 * (1.0f - e2);
-      }
+      const float pw = psi * wT1;
+      tg[0] = ffma(psi, wT0, ffma(-D.omc, q0, t[0]));
+      tg[1] = ffma(ffma(5.0f, ur, 1.0f), pw, ffma(-R.omT1, ffma(-wT1, e1, q1), t[1]));
+      tg[2] = ffma(ffma(5.0f, uz, 1.0f), pw, ffma(-D.omc, ffma(-wT1, e2, q2), t[2]));
+      tg[3] = ffma(ffma(-5.0f, ur, 1.0f), pw, ffma(-R.omT3, ffma(wT1, e1, q3), t[3]));
+      tg[4] = ffma(ffma(-5.0f, uz, 1.0f), pw, ffma(-D.omc, ffma(wT1, e2, q4), t[4]));
     }
     for (int q = 0; q < 5; ++q) B.t[q] = t[q];
 
@@ -1443,7 +1303,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
 #if defined(__HIP_DEVICE_COMPILE__)
         if constexpr (sizeof(S) == 2) asm volatile("" : "+v"(rw), "+v"(wlw));
 #endif
-        wall_lane_inputs<EX, sizeof(S) == 2>(D, B, t, rw, wlw, k, plane_index<BUF, S>(D, row0 + jw), dw, Xw, ga, Tb);
+        wall_lane_inputs<sizeof(S) == 2>(D, B, t, rw, wlw, k, plane_index<BUF, S>(D, row0 + jw), dw, Xw, ga, Tb);
 #pragma unroll
         for (int i = 0; i < 9; ++i) d[i] = isw ? dw[i] : d[i];
 #pragma unroll
@@ -1464,7 +1324,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
     }
 
     // ---- back-transform (Eq. 22) ------------------------------------------
-    back_transform<EX>(d, X[0], X[1], X[2], X[3], X[4], X[5], X[6], X[7]);
+    back_transform(d, X[0], X[1], X[2], X[3], X[4], X[5], X[6], X[7]);
 
     // ---- stream and store --------------------------------------------------
     if constexpr (sizeof(S) == 4) {
@@ -1567,7 +1427,7 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
         if (dr == 0 && dz == 0) continue;
         if (dz == 0 && ((dr == -1 && !rad_m) || (dr == 1 && !rad_p))) continue;
         if ((dz == -1 && !own_zm) || (dz == 1 && !own_zp)) continue;
-        wall_node<S, ODD, MODE>(D, P, B, R.r, j, k, dr, dz, mac_slot, fo, rn);
+        wall_node<S, ODD, MODE, WL>(D, P, B, R.r, j, k, dr, dz, mac_slot, fo, rn);
       }
     }
   }

@@ -239,12 +239,15 @@ struct TileLaunch {
   const InstDev *src, *dst;
   const StepTile* tiles;
   const int* status;
-  int ntiles, nf, nt, lds_bytes;  // nf: fluid threads of the nt of a block
+  int ntiles, lds_bytes;
   hipStream_t stream;
 };
 template <typename S>
-hipError_t launch_tile_t(const TileLaunch& L, int nsteps, long long t) {
-  k_tile<S><<<L.ntiles, L.nt, L.lds_bytes, L.stream>>>(L.src, L.dst, L.tiles, L.status, TILE_VWLOG, L.nf, nsteps, t);
+hipError_t launch_tile_t(bool wall_lanes, const TileLaunch& L, int nsteps, long long t) {
+  if (wall_lanes)
+    k_tile<S, true><<<L.ntiles, TILE_NT, L.lds_bytes, L.stream>>>(L.src, L.dst, L.tiles, L.status, TILE_VWLOG, nsteps, t);
+  else
+    k_tile<S, false><<<L.ntiles, TILE_NT, L.lds_bytes, L.stream>>>(L.src, L.dst, L.tiles, L.status, TILE_VWLOG, nsteps, t);
   return hipGetLastError();
 }
 
@@ -254,7 +257,7 @@ hipError_t launch_step_s16(int storage, bool buf, bool wall_lanes, bool odd, int
                            int mac_slot, uint32_t seed, const long long* clk, int off);
 hipError_t launch_fields_s16(int storage, long long t, const long long* t_stop, const StepLaunch& L, const FieldOut& fo);
 hipError_t launch_pattern_s16(int storage, bool buf, bool odd, const StepLaunch& L, uint32_t key);
-hipError_t launch_tile_s16(int storage, const TileLaunch& L, int nsteps, long long t);
+hipError_t launch_tile_s16(int storage, bool wall_lanes, const TileLaunch& L, int nsteps, long long t);
 hipError_t launch_init_s16(int storage, const StepLaunch& L, const float* dinit, float T_init, int inst);
 
 }  // namespace lbmaxi

@@ -40,9 +40,9 @@ hipError_t launch_pattern_s16(int storage, bool buf, bool odd, const StepLaunch&
              : launch_pattern_t<__hip_bfloat16, false>(odd, L, key);
 }
 
-hipError_t launch_tile_s16(int storage, const TileLaunch& L, int nsteps, long long t) {
-  if (storage == LBM_STORE_FP16) return launch_tile_t<__half>(L, nsteps, t);
-  return launch_tile_t<__hip_bfloat16>(L, nsteps, t);
+hipError_t launch_tile_s16(int storage, bool wall_lanes, const TileLaunch& L, int nsteps, long long t) {
+  if (storage == LBM_STORE_FP16) return launch_tile_t<__half>(wall_lanes, L, nsteps, t);
+  return launch_tile_t<__hip_bfloat16>(wall_lanes, L, nsteps, t);
 }
 
 hipError_t launch_init_s16(int storage, const StepLaunch& L, const float* dinit, float T_init, int inst) {

@@ -208,6 +208,8 @@ __host__ __device__ inline TileWalls tile_walls(const InstDev& D, const TileRegi
   w.count = w.radial + w.rows * (w.lo + w.hi);
   return w;
 }
+// Threads that a block sets aside for them: whole waves.
+__host__ __device__ inline int tile_wall_threads(const TileWalls& w) { return (w.count + 63) / 64 * 64; }
 // Boundary node of thread idx: its owner (j, k) and code 3 (dr + 1) + dz + 1; false: none.
 __host__ __device__ inline bool tile_wall(const InstDev& D, const TileRegion& g, const TileWalls& w, int idx, int& j,
                                           int& k, int& code) {
@@ -247,23 +249,23 @@ constexpr int TILE_NT = 512;  // threads of a tile block
 constexpr int TILE_VWLOG = 5, TILE_VW = 1 << TILE_VWLOG;  // columns of a tile with its halo
 
 // nsteps (even) steps from time level t of every tile's instance, planes of src to
-// planes of dst.  The first nf threads of a block take the fluid nodes and the wall
-// lanes, the others one boundary node each (tile_wall).
-template <typename S>
+// planes of dst.  The last waves of a block take one boundary node each (tile_wall),
+// the nf threads before them the fluid nodes and, with WL (as the handle's single
+// steps have it), the radial wall lanes.
+template <typename S, bool WL>
 __global__ __launch_bounds__(TILE_NT) __attribute__((amdgpu_waves_per_eu(4))) void k_tile(const InstDev* __restrict__ src, const InstDev* __restrict__ dst,
                                                   const StepTile* __restrict__ tiles,
-                                                  const int* __restrict__ status, int vwlog, int nf, int nsteps,
+                                                  const int* __restrict__ status, int vwlog, int nsteps,
                                                   long long t) {
   extern __shared__ __attribute__((aligned(16))) unsigned char tile_lds[];
   const StepTile T = tiles[blockIdx.x];
   if (T.inst < 0 || status[T.inst] != RUN) return;
   const InstDev D = src[T.inst];
-  constexpr bool WL = true;
   // vwlog = TILE_VWLOG as an argument: with the constant the compiler hoists ten
   // more registers out of the step loop (FP32, 64 of 128^2: 18.6 and 18.2 us)
   const int vw = 1 << vwlog, c = (int)threadIdx.x & (vw - 1), rg = (int)threadIdx.x >> vwlog;
-  const int RB = (int)blockDim.x >> vwlog, RG = nf >> vwlog;
   const TileRegion g = tile_load_region(D, T, nsteps);
+  const int RB = (int)blockDim.x >> vwlog;
   const InstDev L = tile_desc<S>(D, T, g, vw, tile_lds);
   uint32_t* lds = (uint32_t*)tile_lds;
   int j = g.jl + c;
@@ -273,6 +275,7 @@ __global__ __launch_bounds__(TILE_NT) __attribute__((amdgpu_waves_per_eu(4))) vo
     }
   const FieldOut fo{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   const TileWalls w = tile_walls<WL>(D, g);
+  const int nf = (int)blockDim.x - tile_wall_threads(w), RG = nf >> vwlog;
   const bool walls = w.count > 0;  // the same for the whole block
   if ((int)threadIdx.x < nf) {
     int wl;
