@@ -162,8 +162,9 @@ int lbm_axi_create(const lbm_axi_params* p, int32_t n_inst, const float* const* 
  * Advance every running instance by nsteps time steps (asynchronous on the
  * handle's stream).  Runs of plain steps may be launched several steps at a
  * time, on a second set of population planes that the handle holds for it
- * (only where that is a small share of the device's memory); the state ends in
- * the same place, and results are the same.  At every multiple of check_interval (from the second
+ * (the sets of all handles come to at most a sixteenth of the device's memory;
+ * lbm_axi_set_graph with 0 gives a handle's back); the state ends in
+ * the same place, and results are the same, bit for bit.  At every multiple of check_interval (from the second
  * one on, counting step 0) the residual and the wall Nusselt numbers are
  * computed on the device and the run state updated; instances that stop are
  * skipped from then on.
@@ -389,7 +390,8 @@ int lbm_axi_set_storage(lbm_axi* h, int32_t storage, int32_t storage_shift);
  * steps (starting at an even time level, no check step inside) through one
  * captured HIP graph, replayed on the handle's stream; check steps and the
  * rest are launched one by one.  Results are identical either way.  steps is
- * even, 0..4096; 0 disables graphs; default 32.  Launch timing
+ * even, 0..4096; 0 launches every step by itself (and frees the second set of
+ * planes of lbm_axi_step); default 32.  Launch timing
  * (lbm_axi_set_timing) bypasses the graphs.  Where the library takes several
  * plain steps per launch instead (FP32 storage, and 16-bit storage up to about
  * 400000 nodes; again with identical results, bit for bit), graphs are not used.  Waits for the stream.

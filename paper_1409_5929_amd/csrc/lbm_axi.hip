@@ -30,6 +30,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -93,6 +94,10 @@ __device__ __align__(256) unsigned char scratch[SCRATCH_NODES * 4 + SCRATCH_COLS
 std::mutex g_scratch_mu;
 void* g_scratch[MAX_DEVICES] = {};
 
+// Bytes that the handles of each device hold for their second sets of planes (k_tile):
+// all together at most a sixteenth of its memory (plan_tiles).
+std::atomic<int64_t> g_tile_bytes[MAX_DEVICES];
+
 }  // namespace
 
 struct lbm_axi {
@@ -140,7 +145,7 @@ struct lbm_axi {
   bool buf = false;             // step kernels use buffer addressing (all arrays below 4 GiB)
   bool wall_lanes = false;      // step kernels compute radial wall nodes on their own lanes
   long long* dclk = nullptr;    // device clock of captured step graphs
-  int graph_steps = 32;         // steps per captured graph (0: no graphs)
+  int graph_steps = 32;         // steps per captured graph (0: no graphs, and no tiles)
   // steps on LDS tiles (k_tile): 0 not planned yet, 1 planned, -1 not used
   int tile_plan = 0;
   int tile_m = 0, tile_h = 0;               // most steps per launch, rows per tile
@@ -149,6 +154,7 @@ struct lbm_axi {
   int nsteptiles = 0;
   InstDev* ddesc_b = nullptr;      // descriptors of the second set of planes
   std::vector<std::pair<void*, size_t>> planes_b;  // that set (and ddesc_b), in allocs
+  int64_t tile_bytes = 0;          // its share of g_tile_bytes
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -786,6 +792,8 @@ void drop_tile_plan(lbm_axi* h) {
   h->dsteptiles = nullptr;
   for (auto& b : h->planes_b) release(h, b.first, b.second);
   h->planes_b.clear();
+  g_tile_bytes[h->device] -= h->tile_bytes;
+  h->tile_bytes = 0;
   h->ddesc_b = nullptr;
   h->tile_plan = 0;
 }
@@ -860,6 +868,7 @@ bool build_step_tiles(lbm_axi* h) {
 // FP32 runs 1414 us a step in single steps and 917 on tiles.
 void plan_tiles(lbm_axi* h) {
   h->tile_plan = -1;
+  if (h->graph_steps == 0) return;  // the caller wants one launch per step
   const size_t esz = h->storage == LBM_STORE_FP32 ? 4 : 2;
   size_t bytes = 0;
   double nodes = 0.0;
@@ -872,7 +881,9 @@ void plan_tiles(lbm_axi* h) {
     nodes += (double)D.nr * D.nz;
   }
   if (esz == 2 && nodes > 5e5) return;  // no round of tiles holds them
-  // the second set of planes: at most a sixteenth of the device's memory
+  // The second sets of planes of all handles: at most a sixteenth of the device's
+  // memory, so that a program of many handles holds about as many as without, and
+  // none that would take a quarter of what is free.  A handle without one takes single steps.
   size_t free_b = 0, total = 0;
   if (hipMemGetInfo(&free_b, &total) != hipSuccess || bytes > total / 16 || bytes > free_b / 4) return;
   h->tile_m = nodes <= 1e5 ? 8 : (nodes <= (esz == 4 ? 4e5 : 3e5) ? 6 : 4);
@@ -916,8 +927,10 @@ void plan_tiles(lbm_axi* h) {
   auto aligned = [](size_t n) { return (n + 255) / 256 * 256; };
   size_t all = 0;
   for (const InstDev& D : b) all += aligned((size_t)14 * D.plane * esz) + (esz == 2 ? aligned((size_t)D.plane * 4) : 0);
-  unsigned char* at = (unsigned char*)alloc(all);
-  bool ok = at != nullptr;
+  h->tile_bytes = (int64_t)(all + sizeof(InstDev) * h->n_inst);
+  bool ok = g_tile_bytes[h->device].fetch_add(h->tile_bytes) + h->tile_bytes <= (int64_t)(total / 16);
+  unsigned char* at = ok ? (unsigned char*)alloc(all) : nullptr;
+  ok = at != nullptr;
   for (InstDev& D : b) {
     if (!ok) break;
     D.pop = at;
@@ -1078,12 +1091,12 @@ void lbm_axi_destroy(lbm_axi* h) {
     (void)hipEventDestroy(e.second);
   }
   drop_graph(h);
+  drop_tile_plan(h);
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
   for (void* p : h->allocs) (void)hipFree(p);
   if (h->dtiles) (void)hipFree(h->dtiles);
   if (h->dtiles_odd) (void)hipFree(h->dtiles_odd);
   if (h->dtiles_plain) (void)hipFree(h->dtiles_plain);
-  if (h->dsteptiles) (void)hipFree(h->dsteptiles);
   if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
   delete h;
 }
@@ -1398,6 +1411,8 @@ int lbm_axi_set_graph(lbm_axi* h, int32_t steps) {
     HIPCHK(hipStreamSynchronize(h->stream));
     drop_graph(h);
     h->graph_steps = steps;
+    if (steps == 0) drop_tile_plan(h);
+    if (h->tile_plan <= 0) plan_tiles(h);
     return LBM_AXI_OK;
   });
 }

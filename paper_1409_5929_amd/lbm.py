@@ -397,7 +397,8 @@ class Lattice:
         self.storage = storage
 
     def set_graph(self, steps: int):
-        """Steps per captured step graph (even, 0 disables)."""
+        """Steps per captured step graph (even).  0: every step is launched by itself,
+        and the handle holds no second set of planes for several at a time."""
         _check(self._lib.lbm_axi_set_graph(self._h, int(steps)))
 
     def step_paths(self) -> dict:

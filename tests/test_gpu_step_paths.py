@@ -32,6 +32,57 @@ def test_long_runs_take_tiles_and_short_or_timed_ones_do_not(L, name, storage): 
     lat.close()
 
 
+def test_no_graphs_means_single_launches_and_no_second_planes(L):  # noqa: F811
+    """set_graph(0) gives the memory of the second set of planes back, any other value takes it again."""
+    cfg = li.annulus(nr=96, nz=72, Ra=1e5, Da=1e-3)
+    lat, other = (L.Lattice(cfg, check_interval=0) for _ in range(2))
+    planes = 14 * 128 * 72 * 4  # rows are padded to 64 columns
+    both = lat.info()["device_bytes"]
+    lat.set_graph(0)
+    assert planes <= both - lat.info()["device_bytes"] <= planes + 4096
+    lat.step(40)
+    assert lat.step_paths() == {"single": 40, "graph": 0, "tiles": 0}
+    lat.set_storage("fp32")  # does not bring it back
+    lat.step(2)
+    lat.set_wall_lanes(0)
+    lat.set_wall_lanes(-1)
+    lat.step(8)
+    assert lat.step_paths()["tiles"] == 0 and both - lat.info()["device_bytes"] >= planes
+    lat.set_graph(8)
+    assert lat.info()["device_bytes"] == both
+    lat.step(50)
+    assert lat.step_paths() == {"single": 50, "graph": 0, "tiles": 50}
+    other.step(100)
+    same(lat.fields(0), other.fields(0), "single launches, then tiles")
+    lat.close()
+    other.close()
+
+
+def test_second_planes_of_all_handles_are_bounded(L):  # noqa: F811
+    """Handles that each take a fiftieth of the device's memory: three have second sets of
+    planes (a sixteenth in all), the next ones single steps with the same bits, until one is
+    closed."""
+    import torch
+
+    total = torch.cuda.mem_get_info()[1]
+    nz = total // 50 // (14 * 4 * 8192)
+    cfg = li.annulus(nr=8192, nz=int(nz), Ra=1e5, Da=1e-3)
+    planes = 14 * 4 * 8192 * int(nz)
+    held = lambda lat: lat.info()["device_bytes"] // planes  # noqa: E731
+    lats = [L.Lattice(cfg, check_interval=0) for _ in range(5)]
+    assert [held(lat) for lat in lats] == [2, 2, 2, 1, 1]
+    for lat in (lats[0], lats[4]):
+        lat.step(8)
+    a, b = lats[0].fields_device(0), lats[4].fields_device(0)
+    assert lats[0].step_paths()["tiles"] == 8 and lats[4].step_paths()["tiles"] == 0
+    assert all(torch.equal(a[k], b[k]) for k in a)
+    lats.pop(1).close()
+    lats.append(L.Lattice(cfg, check_interval=0))
+    assert [held(lat) for lat in lats] == [2, 2, 1, 1, 2]
+    for lat in lats:
+        lat.close()
+
+
 def _periodic(nr, nz):
     return dict(li.annulus(nr=nr, nz=nz, Ra=1e4, Da=1e-2), r0=200.0, side_rmin="periodic", side_rmax="periodic",
                 side_z="periodic", accel_z=1e-5)
