@@ -146,7 +146,7 @@ struct lbm_axi {
   bool wall_lanes = false;      // step kernels compute radial wall nodes on their own lanes
   long long* dclk = nullptr;    // device clock of captured step graphs
   int graph_steps = 32;         // steps per captured graph (0: no graphs, and no tiles)
-  // steps on LDS tiles (k_tile): 0 not planned yet, 1 planned, -1 not used
+  // steps on LDS tiles (k_tile): 0 to be planned by the call that set it, 1 planned, -1 not used
   int tile_plan = 0;
   int tile_m = 0, tile_h = 0;               // most steps per launch, rows per tile
   int tile_lds = 0;                         // LDS bytes of a block
@@ -866,8 +866,9 @@ bool build_step_tiles(lbm_axi* h) {
 // and its fused products are the same, and so is who computes the radial walls (the
 // handle's wall-lane setting).  A wide grid without wall lanes gains as much: 8192^2
 // FP32 runs 1414 us a step in single steps and 917 on tiles.
-void plan_tiles(lbm_axi* h) {
-  h->tile_plan = -1;
+// The calls that change what it rests on (creation, storage, wall lanes, graphs) plan
+// anew before they return, so that a step never allocates or waits.
+void choose_tiles(lbm_axi* h) {
   if (h->graph_steps == 0) return;  // the caller wants one launch per step
   const size_t esz = h->storage == LBM_STORE_FP32 ? 4 : 2;
   size_t bytes = 0;
@@ -949,20 +950,30 @@ void plan_tiles(lbm_axi* h) {
   h->tile_plan = ok ? 1 : -1;
 }
 
+// Whatever fails, host memory included, single steps need none of it.
+void plan_tiles(lbm_axi* h) {
+  h->tile_plan = -1;
+  try {
+    choose_tiles(h);
+  } catch (const std::bad_alloc&) {
+    drop_tile_plan(h);
+    h->tile_plan = -1;
+  }
+}
+
 // Plain steps from the handle's level n that one run on tiles may take: an even
 // number from an even level up to n_end or the next check step, 0 where the
 // handle takes single steps.  A stream that is being captured gets single steps:
 // a replay must not depend on which planes hold the state.
 int tile_run(lbm_axi* h, long long n_end) {
   const long long n = h->t;
-  if (h->timing || (n & 1)) return 0;
+  if (h->tile_plan <= 0 || h->timing || (n & 1)) return 0;
   long long m = n_end - n;
   if (h->check > 0) m = std::min(m, (n + h->check - 1) / h->check * h->check - n);
   if (m < 4) return 0;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(h->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return 0;
-  if (h->tile_plan == 0) plan_tiles(h);
-  return h->tile_plan > 0 ? (int)std::min<long long>(m & ~1ll, 1 << 20) : 0;
+  return (int)std::min<long long>(m & ~1ll, 1 << 20);
 }
 
 // n (even, at least 4) steps on tiles in an even number of launches: the planes
@@ -1486,6 +1497,10 @@ int lbm_axi_set_storage(lbm_axi* h, int32_t storage, int32_t storage_shift) {
     HIPCHK(hipStreamSynchronize(h->stream));
     drop_graph(h);
     drop_tile_plan(h);
+    struct Replan {  // whether or not the conversion succeeds
+      lbm_axi* h;
+      ~Replan() { plan_tiles(h); }
+    } replan{h};
     const int from = h->storage;
     const size_t esz_o = from == LBM_STORE_FP32 ? 4 : 2;
     const size_t esz_n = storage == LBM_STORE_FP32 ? 4 : 2;
@@ -1578,6 +1593,7 @@ int lbm_axi_set_wall_lanes(lbm_axi* h, int32_t mode, int32_t* on) {
     if (want != h->wall_lanes) drop_graph(h);  // captured graphs hold the other kernels
     if (want != h->wall_lanes) drop_tile_plan(h);  // as tiles do
     h->wall_lanes = want;
+    if (h->tile_plan == 0) plan_tiles(h);
     if (on) *on = want ? 1 : 0;
     return LBM_AXI_OK;
   });

@@ -58,6 +58,22 @@ def test_no_graphs_means_single_launches_and_no_second_planes(L):  # noqa: F811
     other.close()
 
 
+@pytest.mark.parametrize("change", ["storage", "wall lanes"])
+def test_a_step_allocates_nothing(L, change):  # noqa: F811
+    """What the second set of planes rests on may change under a handle: the call that
+    changes it takes the new set, not the next step."""
+    lat = L.Lattice(li.annulus(nr=96, nz=72, Ra=1e5, Da=1e-3), storage="fp16", check_interval=0)
+    lat.step(20)
+    if change == "storage":
+        lat.set_storage("fp32")
+    else:
+        lat.set_wall_lanes(0)
+    held = lat.info()["device_bytes"]
+    lat.step(20)
+    assert lat.step_paths()["tiles"] == 40 and lat.info()["device_bytes"] == held
+    lat.close()
+
+
 def test_second_planes_of_all_handles_are_bounded(L):  # noqa: F811
     """Handles that each take a fiftieth of the device's memory: three have second sets of
     planes (a sixteenth in all), the next ones single steps with the same bits, until one is
