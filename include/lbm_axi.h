@@ -179,7 +179,9 @@ int lbm_axi_step(lbm_axi* h, int32_t nsteps);
  * Wall nodes report u = 0, their wall temperature and the density of the
  * neighbour they are built from.  dst_is_device: 1 if the pointers are device
  * memory (written on the handle's stream, not waited for), 0 for host memory
- * (the call waits).
+ * (the call waits).  This call and the ones below that read fields fail with
+ * LBM_AXI_EDEVICE while the handle's stream is being captured: what they launch
+ * follows the parity of the current time level.
  */
 int lbm_axi_macros(lbm_axi* h, int32_t inst, float* uz, float* ur, float* p, float* T,
                    uint8_t* mask, int32_t dst_is_device);
@@ -215,8 +217,8 @@ int lbm_axi_stream_function(lbm_axi* h, int32_t inst, float* psi, double* psi_ab
 
 /*
  * lbm_axi_stream_function for callers that cannot allocate device memory
- * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): the same result without any allocation.  psi: NULL or device
+ * (tight serving loops, harnesses that forbid hipMalloc): the same result
+ * without any allocation.  psi: NULL or device
  * memory for [nz][nr] floats; psi_absmax: NULL or device memory for one
  * double (max |psi|).  Both are written on the handle's stream and not waited
  * for.  Its scratch (the u_z field and the per-column maxima) is a static
@@ -224,9 +226,10 @@ int lbm_axi_stream_function(lbm_axi* h, int32_t inst, float* psi, double* psi_ab
  * most 2^23 nodes and 2^16 columns: a larger instance gets LBM_AXI_EINVAL.
  * All handles on one device share that array and each call leaves its
  * contents behind, so calls that overlap on one device (handles on different
- * streams, threads) race; calls ordered on one stream do not.  The call reads
- * the instance's run state and time level from the device (a small copy to
- * the host, as lbm_axi_info).
+ * streams, threads) race; calls ordered on one stream do not.  For an instance
+ * of more than 8192 step tiles (lbm_axi_set_tiles; 64 columns by up to 32 rows)
+ * on a handle that checks, the call first reads its run state and time level
+ * from the device (a small copy to the host, as lbm_axi_info).
  */
 int lbm_axi_stream_function_static(lbm_axi* h, int32_t inst, float* psi, double* psi_absmax);
 

@@ -597,12 +597,23 @@ int launch_step(lbm_axi* h, bool buf, bool odd, int mode, const StepLaunch& L, i
   return launch_result(e, "step kernel launch");
 }
 
+// Whether the handle's stream is being captured (or cannot be asked).
+bool capturing(const lbm_axi* h) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(h->stream, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Fields of one instance at its own level.  Reading the level back from the device
 // first cost 30 us a call (two copies and a wait, of 57 in all for 64^2); the
 // launch of both parities, of which one returns at once, costs a few.  A handle that
 // never checks has only running instances, and on grids of many blocks the idle
-// launch costs more than the copy.
+// launch costs more than the copy.  The handle's parity is part of the launch, so a
+// graph that recorded it would read the wrong slots when replayed at the other one: a
+// stream that is being captured is refused, at every size.
 int launch_fields(lbm_axi* h, int inst, const FieldOut& fo) {
+  if (capturing(h)) return fail(LBM_AXI_EDEVICE, "fields on a stream that is being captured");
   const StepLaunch L = inst_launch(h, inst);
   long long t = h->t;
   const long long* t_stop = nullptr;
@@ -970,9 +981,7 @@ int tile_run(lbm_axi* h, long long n_end) {
   if (h->tile_plan <= 0 || h->timing || (n & 1)) return 0;
   long long m = n_end - n;
   if (h->check > 0) m = std::min(m, (n + h->check - 1) / h->check * h->check - n);
-  if (m < 4) return 0;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(h->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return 0;
+  if (m < 4 || capturing(h)) return 0;
   return (int)std::min<long long>(m & ~1ll, 1 << 20);
 }
 
