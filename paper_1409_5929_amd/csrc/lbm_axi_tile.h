@@ -67,9 +67,14 @@ __host__ __device__ inline TileRegion tile_load_region(const InstDev& D, const S
 // rows beyond its tile, and no row may be more than one period away (tile_row).
 inline int tile_max_steps(const InstDev& D) { return D.side_z == SIDE_PERIODIC ? D.nz & ~1 : 1 << 20; }
 
-// Whether a tile's region for m steps lies in the rows and columns that stand for
-// the instance's nodes: what k_tile reads then lies in the instance's planes.
+// Whether a tile's regions for up to m steps lie in the rows and columns that stand for
+// the instance's nodes (what k_tile reads then lies in the instance's planes), and none
+// ends beside a radial wall column that it leaves out: the boundary nodes next to that
+// column count it as a wall (whom they send to, and with which random bits), so a region
+// holds the wall or stays clear of its owners.
 inline bool tile_inside(const InstDev& D, const StepTile& T, int m) {
+  if (D.side_rmin == SIDE_WALL && T.j0 > 0 && T.j0 <= m + 1) return false;
+  if (D.side_rmax == SIDE_WALL && T.j1 < D.nr && T.j1 + m >= D.nr - 1) return false;
   const TileRegion g = tile_load_region(D, T, m);
   return g.jl >= 0 && g.jh <= D.nr && g.kl >= 0 && g.kh <= (tile_unwrapped(D, T) ? 3 * D.nz : D.nz) && T.j0 >= g.jl &&
          T.j1 <= g.jh;
@@ -99,9 +104,7 @@ __host__ __device__ inline size_t tile_bytes(size_t n) {
 }
 
 // Descriptor of region g held at lds in rows of vw nodes: the instance's, with
-// its planes in LDS.  A radial wall whose column lies just outside the region
-// is taken out: the fluid nodes beside it are then at the region's edge,
-// where no later step reads what the wall sends.
+// its planes in LDS.
 template <typename S>
 __host__ __device__ inline InstDev tile_desc(const InstDev& D, const StepTile& T, const TileRegion& g, int vw,
                                              unsigned char* lds) {
@@ -114,8 +117,6 @@ __host__ __device__ inline InstDev tile_desc(const InstDev& D, const StepTile& T
   L.pop = lds;
   L.g0 = (float*)lds + TileNode<S>::G0;
   L.phi = (const float*)lds + TileNode<S>::PHI;
-  if (D.side_rmin == SIDE_WALL && g.jl == 1) L.side_rmin = SIDE_PERIODIC;
-  if (D.side_rmax == SIDE_WALL && g.jh == D.nr - 1) L.side_rmax = SIDE_PERIODIC;
   if (tile_unwrapped(D, T)) {
     L.side_z = SIDE_UNWRAPPED;
     L.nz = 4 * D.nz;
