@@ -985,25 +985,18 @@ int tile_run(lbm_axi* h, long long n_end) {
   return (int)std::min<long long>(m & ~1ll, 1 << 20);
 }
 
-// n (even, at least 4) steps on tiles in an even number of launches: the planes
-// alternate, and the state ends in those where it began.
+// n (even, at least 4) steps on tiles (tile_pairs).
 int tile_steps(lbm_axi* h, int n) {
-  const int L = (n + 2 * h->tile_m - 1) / (2 * h->tile_m) * 2;
-  int done = 0;
-  for (int i = 0; i < L; ++i) {
-    const int s = 2 * (int)((int64_t)(n / 2) * (i + 1) / L) - done;
-    const TileLaunch t{i & 1 ? h->ddesc_b : h->ddesc, i & 1 ? h->ddesc : h->ddesc_b, h->dsteptiles, h->dstatus,
+  const long long t0 = h->t;
+  const int rc = tile_pairs(h->t, n, h->tile_m, [&](int i, int steps, long long t) {
+    const TileLaunch L{i & 1 ? h->ddesc_b : h->ddesc, i & 1 ? h->ddesc : h->ddesc_b, h->dsteptiles, h->dstatus,
                        h->nsteptiles, h->tile_lds, h->stream};
-    const hipError_t e = h->storage == LBM_STORE_FP32
-                             ? launch_tile_t<float>(h->wall_lanes, t, s, h->t + done)
-                             : launch_tile_s16(h->storage, h->wall_lanes, t, s, h->t + done);
-    const int rc = launch_result(e, "tile kernel launch");
-    if (rc) return rc;
-    done += s;
-  }
-  h->steps_by[2] += n;
-  h->t += n;
-  return LBM_AXI_OK;
+    return launch_result(h->storage == LBM_STORE_FP32 ? launch_tile_t<float>(h->wall_lanes, L, steps, t)
+                                                      : launch_tile_s16(h->storage, h->wall_lanes, L, steps, t),
+                         "tile kernel launch");
+  });
+  h->steps_by[2] += h->t - t0;
+  return rc;
 }
 
 // One step of instance inst alone, in the AA layout of parity `odd` (plain

@@ -246,6 +246,25 @@ __host__ __device__ inline bool tile_wall_in(const TileRegion& a, int j, int k, 
   return jb >= a.jl && jb < a.jh && k >= a.kl && k < a.kh;
 }
 
+// n (even) steps from level t in launches of at most m, each an even number: launch(i,
+// steps, level) is the i-th and returns 0 or an error, which ends the run.  The planes alternate,
+// so the launches come in pairs and t moves with each pair: whatever fails, the
+// handle's own planes hold the state of level t.
+template <typename Launch>
+int tile_pairs(long long& t, int n, int m, Launch&& launch) {
+  const int pairs = (n + 2 * m - 1) / (2 * m);
+  int done = 0;
+  for (int i = 0; i < 2 * pairs; i += 2) {
+    const int mid = 2 * (int)((int64_t)(n / 2) * (i + 1) / (2 * pairs));
+    const int end = 2 * (int)((int64_t)(n / 2) * (i + 2) / (2 * pairs));
+    if (const int rc = launch(i, mid - done, t)) return rc;
+    if (const int rc = launch(i + 1, end - mid, t + (mid - done))) return rc;
+    t += end - done;
+    done = end;
+  }
+  return 0;
+}
+
 constexpr int TILE_NT = 512;  // threads of a tile block
 constexpr int TILE_VWLOG = 5, TILE_VW = 1 << TILE_VWLOG;  // columns of a tile with its halo
 
