@@ -206,13 +206,13 @@ __global__ __launch_bounds__(RB) void k_convert(const InstDev Di, const InstDev 
   const float dT = Di.T_s - Do.T_s;
 #pragma unroll
   for (int q = 0; q < 9; ++q)
-    Store<So>::st(Q, slot_elem<So>(q, o, pl), Store<Si>::ld(P, slot_elem<Si>(q, o, pl), Di.st_inv),
+    Store<So>::st(Q, slot_elem<So>(q, o, pl), Store<Si>::ld(P, slot_elem<Si>(q, o, pl)) * Di.st_inv,
                   Do.st_scale);
   const float g0 = Di.g0[o] + WT0 * dT;
 #pragma unroll
   for (int q = 1; q < 5; ++q)
     Store<So>::st(Q, slot_elem<So>(9 + q, o, pl),
-                  Store<Si>::ld(P, slot_elem<Si>(9 + q, o, pl), Di.st_inv) + WT1 * dT, Do.st_scale);
+                  Store<Si>::ld(P, slot_elem<Si>(9 + q, o, pl)) * Di.st_inv + WT1 * dT, Do.st_scale);
   Do.g0[o] = g0;  // after the loads: in FP32 both g_0 planes may be plane 9 of one array
 }
 

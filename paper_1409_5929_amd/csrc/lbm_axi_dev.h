@@ -127,7 +127,7 @@ template <typename S>
 struct Store;
 template <>
 struct Store<float> {
-  __host__ __device__ static inline float ld(const float* p, int64_t i, float) { return p[i]; }
+  __host__ __device__ static inline float ld(const float* p, int64_t i) { return p[i]; }
   __host__ __device__ static inline void st(float* p, int64_t i, float v, float) { p[i] = v; }
   __host__ __device__ static inline void st_sr(float* p, int64_t i, float v, float, uint32_t) {
     p[i] = v;
@@ -135,9 +135,7 @@ struct Store<float> {
 };
 template <>
 struct Store<__half> {
-  __host__ __device__ static inline float ld(const __half* p, int64_t i, float inv) {
-    return __half2float(p[i]) * inv;
-  }
+  __host__ __device__ static inline float ld(const __half* p, int64_t i) { return __half2float(p[i]); }
   __host__ __device__ static inline void st(__half* p, int64_t i, float v, float sc) {
     p[i] = __float2half_rn(v * sc);
   }
@@ -154,9 +152,7 @@ struct Store<__half> {
 };
 template <>
 struct Store<__hip_bfloat16> {
-  __host__ __device__ static inline float ld(const __hip_bfloat16* p, int64_t i, float inv) {
-    return __bfloat162float(p[i]) * inv;
-  }
+  __host__ __device__ static inline float ld(const __hip_bfloat16* p, int64_t i) { return __bfloat162float(p[i]); }
   __host__ __device__ static inline void st(__hip_bfloat16* p, int64_t i, float v, float sc) {
     p[i] = __float2bfloat16(v * sc);
   }
@@ -216,7 +212,8 @@ __host__ __device__ inline int64_t slot_elem(int q, int64_t o, int64_t pl) {
 // the population array is below 4 GiB.  The hardware takes the record count
 // and the offsets as unsigned 32-bit values; the builtins declare them int,
 // so values of 2^31 and above pass as their bit patterns.
-// ld / st: slot q of node o.  ld_pair / st_pair: slots a + 1 and a + 10 of
+// ld / st: slot q of node o; ld returns the value as stored, without the storage's
+// inverse scale (node_update_loaded).  ld_pair / st_pair: slots a + 1 and a + 10 of
 // node o (a = 0..3), one 32-bit access in 16-bit storage; the two stochastic
 // roundings fill the low and the high half of the stored word.
 template <typename S>
@@ -232,14 +229,14 @@ __device__ inline uint32_t pack_sr(float f, float g, uint32_t rf, uint32_t rg) {
   }
 }
 template <typename S>
-__device__ inline void unpack(uint32_t w, float inv, float& f, float& g) {
+__device__ inline void unpack(uint32_t w, float& f, float& g) {
   if constexpr (std::is_same<S, __half>::value) {
     const lbm_h2 h = __builtin_bit_cast(lbm_h2, w);
-    f = (float)h[0] * inv;
-    g = (float)h[1] * inv;
+    f = (float)h[0];
+    g = (float)h[1];
   } else {
-    f = __uint_as_float(w << 16) * inv;
-    g = __uint_as_float(w & 0xFFFF0000u) * inv;
+    f = __uint_as_float(w << 16);
+    g = __uint_as_float(w & 0xFFFF0000u);
   }
 }
 
@@ -275,17 +272,17 @@ struct PopAcc<S, ADDR_FLAT> {
   static constexpr int ADDR = ADDR_FLAT;
   S* P;
   int64_t pl;
-  float inv, sc;
+  float sc;
   __host__ __device__ explicit PopAcc(const InstDev& D)
-      : P((S*)D.pop), pl(D.plane), inv(D.st_inv), sc(D.st_scale) {}
-  __host__ __device__ float ld(int q, int64_t o) const { return Store<S>::ld(P, slot_elem<S>(q, o, pl), inv); }
+      : P((S*)D.pop), pl(D.plane), sc(D.st_scale) {}
+  __host__ __device__ float ld(int q, int64_t o) const { return Store<S>::ld(P, slot_elem<S>(q, o, pl)); }
   __host__ __device__ void st(int q, int64_t o, float v, uint32_t r) const {
     Store<S>::st_sr(P, slot_elem<S>(q, o, pl), v, sc, r);
   }
   __host__ __device__ void ld_pair(int a, int64_t o, float& f, float& g) const {
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (sizeof(S) == 2) {
-      unpack<S>(((const uint32_t*)P)[(int64_t)(5 + 2 * a) * (pl >> 1) + o], inv, f, g);
+      unpack<S>(((const uint32_t*)P)[(int64_t)(5 + 2 * a) * (pl >> 1) + o], f, g);
       return;
     }
 #endif
@@ -310,8 +307,8 @@ struct PopAcc<S, ADDR_BUF> {
   __amdgpu_buffer_rsrc_t rs;
 #endif
   int64_t pl;
-  float inv, sc;
-  __host__ __device__ explicit PopAcc(const InstDev& D) : pl(D.plane), inv(D.st_inv), sc(D.st_scale) {
+  float sc;
+  __host__ __device__ explicit PopAcc(const InstDev& D) : pl(D.plane), sc(D.st_scale) {
 #if defined(__HIP_DEVICE_COMPILE__)
     rs = __builtin_amdgcn_make_buffer_rsrc(D.pop, (short)0, (int)(uint32_t)D.pop_bytes, 0x00020000);
 #endif
@@ -324,9 +321,9 @@ struct PopAcc<S, ADDR_BUF> {
     } else {
       const uint16_t b = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)off, 0, 0);
       if constexpr (std::is_same<S, __half>::value)
-        return __half2float(__builtin_bit_cast(__half, b)) * inv;
+        return __half2float(__builtin_bit_cast(__half, b));
       else
-        return __uint_as_float((uint32_t)b << 16) * inv;
+        return __uint_as_float((uint32_t)b << 16);
     }
 #else
     (void)q;
@@ -358,7 +355,7 @@ struct PopAcc<S, ADDR_BUF> {
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (sizeof(S) == 2) {
       const uint32_t off = (uint32_t)((int64_t)(5 + 2 * a) * pl + 2 * o) * 2u;
-      unpack<S>((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0), inv, f, g);
+      unpack<S>((uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 0), f, g);
       return;
     }
 #endif
@@ -386,17 +383,17 @@ struct PopAcc<S, ADDR_TILE> {
   using N = TileNode<S>;
   S* P;
   int base;
-  float inv, sc;
-  __host__ __device__ explicit PopAcc(const InstDev& D) : P((S*)D.pop), base(D.t_base), inv(D.st_inv), sc(D.st_scale) {}
+  float sc;
+  __host__ __device__ explicit PopAcc(const InstDev& D) : P((S*)D.pop), base(D.t_base), sc(D.st_scale) {}
   __host__ __device__ int at(int64_t o) const { return mul24((int)o - base, N::WORDS * 4 / (int)sizeof(S)); }
-  __host__ __device__ float ld(int q, int64_t o) const { return Store<S>::ld(P, at(o) + N::slot(q), inv); }
+  __host__ __device__ float ld(int q, int64_t o) const { return Store<S>::ld(P, at(o) + N::slot(q)); }
   __host__ __device__ void st(int q, int64_t o, float v, uint32_t r) const {
     Store<S>::st_sr(P, at(o) + N::slot(q), v, sc, r);
   }
   __host__ __device__ void ld_pair(int a, int64_t o, float& f, float& g) const {
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (sizeof(S) == 2) {
-      unpack<S>(((const uint32_t*)P)[mul24((int)o - base, N::WORDS) + N::PAIR + a], inv, f, g);
+      unpack<S>(((const uint32_t*)P)[mul24((int)o - base, N::WORDS) + N::PAIR + a], f, g);
       return;
     }
 #endif
@@ -467,7 +464,8 @@ __host__ __device__ inline float ffma(float a, float b, float c) {
 // ---- per-column constants (r is fixed along a thread's z loop) -------------
 struct RowC {
   float r, inv_r;
-  float rp, op1, op5;  // sources of e_r = +1 populations: ratio r_src / r, offsets
+  float rp, op1, op5;  // sources of e_r = +1 populations: ratio r_src / r (times the storage's
+                       // inverse scale, a power of two), offsets
   float rm, om1, om5;  // sources of e_r = -1 populations (offsets vanish unless r wraps)
   float lr0b;          // (1 + c_s^2 (tau - 1/2) / r^2) / 2, Eq. (30) divided by r
   float hcs2r;         // c_s^2 / (2 r), Eq. (29) divided by r rho
@@ -503,8 +501,8 @@ __host__ __device__ inline RowC make_row(const InstDev& D, int j) {
   // d = (r_src / r) s + w (r_src - r + e_r) / r: the offset is zero unless
   // the source sits across a radial wrap (r_src != r - e_r).
   const double invd = 1.0 / rd;
-  R.rp = (float)(src_p * invd);
-  R.rm = (float)(src_m * invd);
+  R.rp = (float)(src_p * invd) * D.st_inv;
+  R.rm = (float)(src_m * invd) * D.st_inv;
   R.op1 = R.op5 = R.om1 = R.om5 = 0.0f;
   if (wrap_p) {
     const double gp = (src_p - rd + 1.0) * invd;
@@ -883,8 +881,8 @@ __host__ __device__ inline void wall_node(const InstDev& D, const A& P, const No
   }
 }
 
-// The populations arriving at fluid node (j, k) (as stored, unscaled to
-// FP32) and its porosity value.  Each slot is read and written by one node
+// The populations arriving at fluid node (j, k) (as stored, in FP32) and its
+// porosity value.  Each slot is read and written by one node
 // only in a step, so these loads may be issued before earlier nodes of the
 // same thread are updated.
 template <typename S, bool ODD, int BUF = ADDR_FLAT>
@@ -1002,7 +1000,8 @@ template <typename S, bool ODD, int BUF>
 __device__ inline void pattern_store(const InstDev& D, const RowC& R, int j, int k, const float s[9],
                                      const float t[5], float ph, uint32_t key) {
   constexpr int OPP[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
-  const PopAcc<S, BUF> P(D);
+  PopAcc<S, BUF> P(D);
+  P.sc = 1.0f;  // back as read
   int q[13];
   int64_t off[13], o;
   node_slots<ODD>(D, R, j, k, q, off, o);
@@ -1144,15 +1143,18 @@ __host__ __device__ inline void node_update_loaded(const InstDev& D, const RowC&
   const int64_t rowm = row_off<BUF>(km, st), row0 = row_off<BUF>(k, st), rowp = row_off<BUF>(kp, st);
   const int64_t o = row0 + j;
   Dither rn(mix32(seed ^ dither_id<BUF>(D, o, j, k, wl)));  // a wall lane draws its wall node's stream
-  float t[5] = {t_in[0], t_in[1], t_in[2], t_in[3], t_in[4]};
+  // Values of 16-bit storage times its inverse scale; the radial ones get it with
+  // their rescaling (RowC), which saves their products: exact, as a power of two.
+  const float inv = sizeof(S) == 4 ? 1.0f : D.st_inv;
+  float t[5] = {t_in[0], t_in[1] * inv, t_in[2] * inv, t_in[3] * inv, t_in[4] * inv};
   float phi, cD, cF;
   porosity_of(D, phi_raw, phi, cD, cF);
 
   // Rescale to this node's frame: d_i = fhat_i - w_i (1 - e_ir / (2 r)).
   float d[9];
-  d[0] = s[0];
-  d[2] = s[2];
-  d[4] = s[4];
+  d[0] = s[0] * inv;
+  d[2] = s[2] * inv;
+  d[4] = s[4] * inv;
   d[1] = ffma(s[1], R.rp, R.op1);
   d[5] = ffma(s[5], R.rp, R.op5);
   d[8] = ffma(s[8], R.rp, R.op5);
