@@ -52,9 +52,9 @@ def kernel_source_sha() -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic(storage: str):
-    """HBM bytes per step-kernel launch from committed rocprofv3 counter runs,
-    if they were taken on the current kernel source."""
+def measured_traffic(storage: str, key: str = "bytes_per_launch"):
+    """HBM bytes per step-kernel launch (or per step of a tile launch) from committed
+    rocprofv3 counter runs, if they were taken on the current kernel source."""
     try:
         with open(TRAFFIC_FILE) as f:
             t = json.load(f)
@@ -63,7 +63,7 @@ def measured_traffic(storage: str):
     e = t.get(storage)
     if not e or t.get("source_sha") != kernel_source_sha():
         return None
-    return e["bytes_per_launch"]
+    return e.get(key)
 
 
 def device_copy_gbs(torch, stream, nbytes: int = 2 << 30, reps: int = 5) -> float:
@@ -451,6 +451,7 @@ def main():
         del src, dst
 
     log(f"timed {args.steps} steps")
+    paths0 = lat.step_paths()
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
@@ -459,6 +460,7 @@ def main():
     e1.record(stream)
     torch.cuda.synchronize()
     total_ms = e0.elapsed_time(e1)
+    paths = {k: v - paths0[k] for k, v in lat.step_paths().items()}
     res = lat.residual()
     info = lat.info()
     # the roofline of one step's kernel, from events around its launches: a handle
@@ -501,6 +503,8 @@ def main():
     avg_ms = kern_ms / max(launches, 1)
     achieved = alg_bytes / (kern_ms * 1e-3) / 1e9
     traffic = measured_traffic(args.storage)
+    tile_traffic = measured_traffic(args.storage, "tile_bytes_per_step")
+    step_s = total_ms * 1e-3 / args.steps
     mlups = n * n * args.steps / (total_ms * 1e-3) / 1e6
     out = {
         "metric": METRIC,
@@ -520,6 +524,16 @@ def main():
                         f"mean 0.6 sd 0.15 sigma 8 clipped [0.3,0.95], Ergun F_phi), cold start, "
                         f"check every {args.check_interval} steps",
             "nr": n, "nz": n, "storage": args.storage, "check_interval": args.check_interval,
+        },
+        # the timed region itself: how its steps were launched, and the rate at which it
+        # moves the bytes of the tile launches that take most of them (counters, where
+        # the kernel sources are those they were taken on)
+        "timed_region": {
+            "steps_by_path": paths,
+            "hbm_bytes_per_tile_step": tile_traffic if paths["tiles"] else None,
+            "hbm_gbs": round(tile_traffic / step_s / 1e9, 1) if tile_traffic and paths["tiles"] else None,
+            "single_step_bytes_gbs": round(fluid * bytes_node / step_s / 1e9, 1),
+            "bound": "vector issue (k_tile)" if paths["tiles"] else "hbm (k_step)",
         },
         "roofline": {
             "bound": "hbm",
