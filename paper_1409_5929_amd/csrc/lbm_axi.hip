@@ -864,19 +864,19 @@ bool build_step_tiles(lbm_axi* h) {
 // work, and the halo, worked on again by each tile, is kept small: 6, then 4 steps
 // on tiles of about 28 rows, two at a time on a unit (34 rows fill half its
 // LDS).  A few such rounds of tiles: as many rows as save a round, no more (64 of
-// 128^2: 20.8 us with 26 rows in 4 rounds, 18.7 with 32 in 3; 1000^2: 17.8 with 28
-// and 18.1 with 34, both 3).
+// 128^2: 19.3 us with 26 rows in 4 rounds, 16.6 with 32 in 3; 1000^2: 16.6 with 28
+// and 16.5 with 34, both 3).
 // Measured, us per step in single steps and on tiles: FP32 pipe 64 x 8 4.1 and
-// 1.7, annulus 100 x 200 7.2 and 2.6, 300^2 8.0 and 4.1, 512^2 11.1 and 6.8, 64
-// of 128^2 30.6 and 18.7, 1000^2 26.5 and 17.8, the first 256 grids of the sweep
-// 449 and 302; FP16 200^2 9.0 and 5.6, 512^2 11.9 and 9.3.  In 16-bit storage
+// 2.0, annulus 100 x 200 7.1 and 2.5, 300^2 8.0 and 3.6, 512^2 10.8 and 6.0, 64
+// of 128^2 30.5 and 16.6, 1000^2 26.5 and 16.6, the first 256 grids of the sweep
+// 450 and 281, 8192^2 (no wall lanes) 1422 and 926; FP16 200^2 9.0 and 5.4, 512^2
+// 12.0 and 8.6, a pipe of 65 x 64 (none either) 7.5 and 3.1.  In 16-bit storage
 // single steps take over where the tiles come to more than one round (FP16 600^2
-// 13.2 and 10.0, four of 300^2 12.2 and 11.0, but 2000^2 55 and 75 at best): they
+// 13.2 and 9.4, four of 300^2 12.1 and 10.3, but 2000^2 53 and 73 at best): they
 // move half the bytes, and the halo's roundings cost more.
 // Every node comes out as in the handle's single steps, bit for bit: the node code
 // and its fused products are the same, and so is who computes the radial walls (the
-// handle's wall-lane setting).  A wide grid without wall lanes gains as much: 8192^2
-// FP32 runs 1414 us a step in single steps and 917 on tiles.
+// handle's wall-lane setting).
 // The calls that change what it rests on (creation, storage, wall lanes, graphs) plan
 // anew before they return, so that a step never allocates or waits.
 void choose_tiles(lbm_axi* h) {

@@ -770,8 +770,8 @@ struct GemmShape {
 // stages: large ones (64 x 256 outputs for M <= 64, else 128 x 128, or 48 and
 // 96 rows where M pads to less) from 512 blocks on, then 64 x 64 ones from 256
 // blocks on, else 32 x 32.  Measured, 128^2 forward of widths from 48: batch 1
-// 265 us with large blocks alone, 160 with 64 x 64 ones, 128 with all three;
-// batch 8 389, 316 and 312.  Every shape adds the products of an output in the
+// 265 us with large blocks alone, 160 with 64 x 64 ones, 128 with all three (116 since
+// the skip input is added in the epilogue); batch 8 389, 316 and 312.  Every shape adds the products of an output in the
 // same order.
 GemmShape gemm_shape(int64_t M, int64_t N, int64_t nz) {
   const GemmShape g4{M <= 64 ? 1 : 2, 4, 4}, g3{g4.wm, 3, 4}, g2{2, 2, 2};
